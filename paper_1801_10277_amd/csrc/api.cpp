@@ -583,7 +583,8 @@ int render(celeste_plan* p, hipStream_t st, bool sums = false) {
 }
 
 // kk: also the pixel-level rows (brightness factors, frac_dev) of every box's intermediate
-// Hessian (double gradient passes on stored backgrounds before hessian_from_intermediates).
+// Hessian (double gradient passes on stored backgrounds before hessian_from_intermediates);
+// with the closed-form Hessian the rest of the gradient's sums comes with those passes.
 int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tangent, int base, bool deriv,
             hipStream_t st, int grid_override = 0, bool kk = false) {
     AdjArgs a{};
@@ -606,6 +607,7 @@ int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tange
     if (kk) {
         // the pass also leaves the listed boxes' own profile values in d_fg for the
         // closed-form Hessian pass, so d_fg no longer holds a render's values
+        a.kk_pixel = p->hess_mode == 0;
         a.fg_out = p->d_fg;
         p->fg_valid = false;
     }
@@ -657,16 +659,18 @@ int background(celeste_plan* p, const Sel& items, hipStream_t st, bool stored = 
     return CELESTE_OK;
 }
 
-// Dense Hessians of the listed sources (d_hess by list position).  Expects the item
+// Dense Hessians of the listed sources (d_hess by list position) and, with `grad`, their
+// gradient rows [S][ROW].  Expects the item
 // partials and pixel-level Hessian rows (kk: brightness factors and frac_dev) of a double
 // gradient pass over `item` on stored backgrounds (and, for the closed-form pass, the
 // own profile values that pass stores).  With the position and shape rows (closed-form
 // pass, or five tangent passes along those intermediates) they give each box's 10x10
 // Hessian of its pixel terms; the chain rule and its tangent assemble the 27x27 blocks.
-// With `active`, the closed-form pass covers only the boxes of the sources it marks (the
-// other sources' blocks are left undefined).
+// With `active`, only the sources it marks are covered (the other sources' blocks and
+// gradients are left as they were).
 int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& src, const Sel& pair, const Sel& item,
-                               int base, double* hess, hipStream_t st, const uint8_t* active = nullptr);
+                               int base, double* hess, double* grad, hipStream_t st,
+                               const uint8_t* active = nullptr);
 
 #define CHK(x)                              \
     do {                                    \
@@ -855,13 +859,12 @@ int render_stored(celeste_plan* p, const double* theta, const Scope& render, hip
 }
 
 int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& src, const Sel& pair, const Sel& item,
-                               int base, double* hess, hipStream_t st, const uint8_t* active) {
-    HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, p->d_kk, false, 0, p->d_gw, p->d_hw, p->d_status,
-                              st));
+                               int base, double* hess, double* grad, hipStream_t st, const uint8_t* active) {
     // the brightness-factor and frac_dev rows came with the gradient pass; the five position
     // and shape rows (by symmetry, the other rows' remaining entries too) come from the
     // closed-form pass over the stored backgrounds, or from tangent passes of the adjoint
-    if (p->hess_mode == 0 && base == BASE_BG) {
+    const bool closed = p->hess_mode == 0 && base == BASE_BG;
+    if (closed) {
         AdjArgs a{};
         a.g = p->geom();
         a.items = item;
@@ -870,23 +873,27 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.coef = p->d_coef1;
         a.bg = p->d_bg;
         a.fg = p->d_fg;
+        a.partials = p->d_partials;
         a.dynamic = p->dynamic;
         a.counter = p->d_counter;
         a.status = p->d_status;
         HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->wpb, p->rows, st));
+    }
+    HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, p->d_kk, false, 0, p->d_gw, p->d_hw, p->d_status,
+                              st));
+    if (closed) {
         HIPCHK(launch_pair_hess(pair, p->d_pairs, p->d_hg, p->d_hw, p->d_status, st));
-        HIPCHK(launch_assemble_hessian(src, p->geom(), p->d_patch_ptr, theta, p->d_gw, p->d_hw, hess, p->d_status,
-                                       st));
-        return CELESTE_OK;
+    } else {
+        for (int i = W_UX; i < NW; ++i) {
+            if (i == W_FDEV) continue;
+            CHK(prep(p, theta, pair, true, DIR_W, nullptr, i, st));
+            CHK(adjoint(p, item, nullptr, true, base, true, st));
+            HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, nullptr, true, i, p->d_gw, p->d_hw,
+                                      p->d_status, st));
+        }
     }
-    for (int i = W_UX; i < NW; ++i) {
-        if (i == W_FDEV) continue;
-        CHK(prep(p, theta, pair, true, DIR_W, nullptr, i, st));
-        CHK(adjoint(p, item, nullptr, true, base, true, st));
-        HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, nullptr, true, i, p->d_gw, p->d_hw, p->d_status,
-                                  st));
-    }
-    HIPCHK(launch_assemble_hessian(src, p->geom(), p->d_patch_ptr, theta, p->d_gw, p->d_hw, hess, p->d_status, st));
+    HIPCHK(launch_assemble_hessian(src, p->geom(), p->d_patch_ptr, theta, p->d_gw, p->d_hw, hess, grad, active,
+                                   p->d_status, st));
     return CELESTE_OK;
 }
 
@@ -927,24 +934,24 @@ int newton_run(celeste_plan* p, double* theta, const Sel& src, const Sel& pair, 
     // value, gradient and Hessian at the entry point
     CHK(prep(p, theta, pair, false, DIR_NONE, nullptr, 0, st));
     CHK(adjoint(p, item, nullptr, false, BASE_BG, true, st, 0, true));
-    CHK(finalize(p, theta, src, nullptr, false, DIR_NONE, nullptr, 0, true, p->d_elbo_cur, p->d_grad, nullptr, 0,
+    CHK(finalize(p, theta, src, nullptr, false, DIR_NONE, nullptr, 0, false, p->d_elbo_cur, nullptr, nullptr, 0,
                  false, st));
-    CHK(hessian_from_intermediates(p, theta, src, pair, item, BASE_BG, p->d_hess, st));
+    CHK(hessian_from_intermediates(p, theta, src, pair, item, BASE_BG, p->d_hess, p->d_grad, st));
     for (int it = 0; it < n_steps; ++it) {
         HIPCHK(launch_tr_solve(tr, st));
-        // the trial point of every source still stepping (d_live): its value and, except
-        // after the last step, its gradient; then, for the sources whose step was accepted,
-        // its Hessian, and gradient and Hessian become the current ones (a rejected step
-        // keeps the point and with it the current gradient and Hessian)
+        // the trial point of every source still stepping (d_live): its value; then, except
+        // after the last step and for the sources whose step was accepted, its gradient and
+        // Hessian, which become the current ones (a rejected step keeps the point and with it
+        // the current gradient and Hessian)
         const bool more = it + 1 < n_steps;
         CHK(prep(p, p->d_theta_trial, pair, false, DIR_NONE, nullptr, 0, st));
         CHK(adjoint(p, item, p->d_live, false, BASE_BG, more, st, 0, more));
-        CHK(finalize(p, p->d_theta_trial, src, p->d_live, false, DIR_NONE, nullptr, 0, more, p->d_elbo_trial,
-                     more ? p->d_grad_trial : nullptr, nullptr, 0, false, st));
+        CHK(finalize(p, p->d_theta_trial, src, p->d_live, false, DIR_NONE, nullptr, 0, false, p->d_elbo_trial,
+                     nullptr, nullptr, 0, false, st));
         HIPCHK(launch_tr_update(tr, st));
         if (more) {
-            CHK(hessian_from_intermediates(p, p->d_theta_trial, src, pair, item, BASE_BG, p->d_hess_trial, st,
-                                           p->d_accepted));
+            CHK(hessian_from_intermediates(p, p->d_theta_trial, src, pair, item, BASE_BG, p->d_hess_trial,
+                                           p->d_grad_trial, st, p->d_accepted));
             HIPCHK(launch_tr_adopt(tr, st));
         }
     }
@@ -1381,7 +1388,7 @@ int celeste_hessian(celeste_plan* p, const double* theta, const int32_t* src, in
         CHK(background(p, si, st));
     }
     CHK(adjoint(p, si, nullptr, false, BASE_BG, true, st, 0, true));
-    CHK(hessian_from_intermediates(p, theta, ss, sp, si, BASE_BG, p->d_hess, st));
+    CHK(hessian_from_intermediates(p, theta, ss, sp, si, BASE_BG, p->d_hess, nullptr, st));
     const size_t np2 = (size_t)p->consts.npar * p->consts.npar;
     HIPCHK(hipMemcpyAsync(hess, p->d_hess, (size_t)n * np2 * sizeof(double), hipMemcpyDeviceToDevice, st));
     return CELESTE_OK;
@@ -1443,8 +1450,10 @@ int celeste_newton(celeste_plan* p, double* theta, const int32_t* src, int n, in
     CHK(fill_u8(p->d_done, ss, 0, st));
     if (stored && n_steps > 0) CHK(render_stored(p, theta, rs, st));
     CHK(newton_run(p, theta, ss, sp, si, n_steps, prm, radius, st, stored && n_steps > 0));
-    if (elbo_out) {
-        // final ELBO_s at the returned point
+    if (elbo_out && n_steps > 0) {
+        // the ELBO_s of the returned point: that of the last accepted trial (or of the entry)
+        HIPCHK(launch_copy_f64_sel(elbo_out, p->d_elbo_cur, ss, p->d_status, st));
+    } else if (elbo_out) {
         CHK(prep(p, theta, sp, false, DIR_NONE, nullptr, 0, st));
         CHK(adjoint(p, si, nullptr, false, BASE_BG, false, st));
         CHK(finalize(p, theta, ss, nullptr, false, DIR_NONE, nullptr, 0, false, elbo_out, nullptr, nullptr, 0, false,

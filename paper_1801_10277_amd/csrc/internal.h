@@ -177,6 +177,8 @@ struct AdjArgs {
     double* partials;          // [n_items_total][NACC] of T
     double* kk;                // [n_items_total][NKK]: brightness-factor block of the box's
                                // intermediate Hessian (double gradient passes), or null
+    int32_t kk_pixel;          // with kk: 1 leaves the position, frac_dev and shape sums of the
+                               // gradient to k_hess_second
     double* fg_out;            // [n_visits][2]: own profile values written by the passes that
                                // fill kk, or null
     const int* status;
@@ -261,9 +263,13 @@ hipError_t launch_pair_reduce(const Sel& pairs, const PairDev* dpairs, const dou
 hipError_t launch_pair_hess(const Sel& pairs, const PairDev* dpairs, const double* hg, double* hw, const int* status,
                             hipStream_t st);
 // 27x27 Hessians of the listed sources (hess by list position) from gw, hw and the KL.
+// grad (or null): also the gradient rows [S][ROW] of the listed sources.  active (or null):
+// only the marked sources.
 hipError_t launch_assemble_hessian(const Sel& srcs, const Geometry& g, const int32_t* patch_ptr,
                                    const double* theta, const double* gw, const double* hw, double* hess,
-                                   const int* status, hipStream_t st);
+                                   double* grad, const uint8_t* active, const int* status, hipStream_t st);
+// out[s] = in[s] of the listed sources.
+hipError_t launch_copy_f64_sel(double* out, const double* in, const Sel& s, const int* status, hipStream_t st);
 
 // Entry point without allocation (noalloc.hip): the batched ELBO + gradient of api.cpp with
 // the per-item partial sums and the work-queue counter at the given device addresses.

@@ -378,13 +378,15 @@ __global__ void __launch_bounds__(128) k_assemble_hessian(Sel srcs, Geometry g, 
                                                           const double* __restrict__ theta,
                                                           const double* __restrict__ gw,
                                                           const double* __restrict__ hw,
-                                                          double* __restrict__ hess, const int* status) {
+                                                          double* __restrict__ hess, double* __restrict__ grad,
+                                                          const uint8_t* __restrict__ active, const int* status) {
     if (*status) return;
     const int npar = g.consts.npar;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= srcs.n * npar) return;
     const int j = t / npar, d = t - j * npar;
     const int s = sel_at(srcs, j);
+    if (active && !active[s]) return;
     dual p[NPK], gh[NPK];
     for (int i = 0; i < NPK; ++i) {
         p[i] = mkd(theta[(size_t)s * ROW + i], i == d ? 1.0 : 0.0);
@@ -417,6 +419,8 @@ __global__ void __launch_bounds__(128) k_assemble_hessian(Sel srcs, Geometry g, 
     if (g.consts.flags & CELESTE_INCLUDE_KL) kl_source<dual>(p, g.consts, gh);
     double* o = hess + (size_t)j * npar * npar + (size_t)d * npar;
     for (int i = 0; i < npar; ++i) o[i] = gh[i].t;
+    if (grad && d == 0)
+        for (int i = 0; i < ROW; ++i) grad[(size_t)s * ROW + i] = i < NPK ? gh[i].v : 0.0;
 }
 
 // Total ELBO: a fixed-order two-level sum.  Block b of k_total_partial sums its contiguous
@@ -482,6 +486,12 @@ __global__ void k_fill_f64_sel(double* p, Sel s, double v) {
     if (j < s.n) p[sel_at(s, j)] = v;
 }
 
+__global__ void k_copy_f64_sel(double* __restrict__ out, const double* __restrict__ in, Sel s, const int* status) {
+    if (*status) return;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < s.n) out[sel_at(s, j)] = in[sel_at(s, j)];
+}
+
 // ----------------------------------------------------------------------- launchers
 hipError_t launch_validate(const double* theta, const uint8_t* active, const int32_t* list, int n,
                            int S, int npar, int* status, hipStream_t st) {
@@ -542,6 +552,12 @@ hipError_t launch_fill_f64_sel(double* p, const Sel& s, double v, hipStream_t st
     return hipGetLastError();
 }
 
+hipError_t launch_copy_f64_sel(double* out, const double* in, const Sel& s, const int* status, hipStream_t st) {
+    if (s.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_copy_f64_sel, dim3((s.n + 255) / 256), dim3(256), 0, st, out, in, s, status);
+    return hipGetLastError();
+}
+
 hipError_t launch_pair_reduce(const Sel& sel, const PairDev* dpairs, const double* partials, const double* kk,
                               bool tangent, int dir, double* gw, double* hw, const int* status, hipStream_t st) {
     if (sel.n <= 0) return hipSuccess;
@@ -558,12 +574,12 @@ hipError_t launch_pair_hess(const Sel& sel, const PairDev* dpairs, const double*
 }
 
 hipError_t launch_assemble_hessian(const Sel& srcs, const Geometry& g, const int32_t* patch_ptr, const double* theta,
-                                   const double* gw, const double* hw, double* hess, const int* status,
-                                   hipStream_t st) {
+                                   const double* gw, const double* hw, double* hess, double* grad,
+                                   const uint8_t* active, const int* status, hipStream_t st) {
     if (srcs.n <= 0) return hipSuccess;
     const int n = srcs.n * g.consts.npar;
     hipLaunchKernelGGL(k_assemble_hessian, dim3((n + 127) / 128), dim3(128), 0, st, srcs, g, patch_ptr, theta, gw,
-                       hw, hess, status);
+                       hw, hess, grad, active, status);
     return hipGetLastError();
 }
 

@@ -605,15 +605,31 @@ __global__ void __launch_bounds__(256) k_render_strips(Sel sel, const Item* __re
 }
 
 // ----------------------------------------------------------------------- adjoint
-// KK (double gradient passes over planes, stored backgrounds or stored values only): also
-// the brightness-factor block of each box's intermediate Hessian, per item into a.kk.
+// KK (double passes over stored backgrounds only): also the brightness-factor and frac_dev
+// block of each box's intermediate Hessian, per item into a.kk, and the own profile values
+// into a.fg_out.  KK_FULL is the whole gradient pass; KK_PIXEL leaves pass B out (the
+// position, frac_dev and shape sums of the gradient come from the row moments that
+// k_hess_second takes anyway), so it holds no row weights and needs no second evaluation of
+// the Gaussians: on 1024 sources (1.6e7 visits) 618 -> 376 us a pass (bounded to three waves
+// per SIMD it spills 71 VGPRs and takes as long), k_hess_second 560 -> 600 us.
 // At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
 // plus accumulation registers and run one wave per SIMD; with the bound they spill a few
 // hundred bytes per lane and run 17% faster (the value variants fit without spilling).
 // Three for the value-gradient pass over stored own values (the hot path): it needs 191
 // VGPRs unbounded and 168 with the bound (two registers spilled).
-template <class T, int BASE, bool DERIV, int L, bool FGM, bool KK>
-__global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>::value) ? 3 : 2) k_adjoint_strips(AdjArgs a, const Item* __restrict__ items,
+// Whether a pass reads each box's table from LDS: the double passes that evaluate Gaussians
+// and take the background from planes, stored backgrounds or stored values.
+template <class T, int BASE, bool DERIV, bool FGM>
+constexpr bool lds_table() {
+    if (!std::is_same<T, double>::value) return false;
+    if (FGM) return DERIV && (BASE == BASE_PLANES || BASE == BASE_FG);
+    return BASE == BASE_BG || (DERIV && BASE == BASE_PLANES);
+}
+
+enum KKMode { KK_NONE = 0, KK_FULL = 1, KK_PIXEL = 2 };
+
+template <class T, int BASE, bool DERIV, int L, bool FGM, int KK>
+__global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV && FGM ? 3 : 2)) k_adjoint_strips(AdjArgs a, const Item* __restrict__ items,
                                                         const PairDev* __restrict__ pairs,
                                                         const celeste_image* __restrict__ images,
                                                         const int32_t* __restrict__ nbr,
@@ -635,8 +651,7 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
     // instead of missing the scalar cache (38% of the scalar loads missed with the table read
     // from global memory), the table leaves the scalar registers (no spills), and the
     // coefficients every lane shares are formed once per box instead of once per strip.
-    constexpr bool LDS_TAB = DERIV && std::is_same<T, double>::value &&
-                             (FGM ? (BASE == BASE_PLANES || BASE == BASE_FG) : (BASE == BASE_PLANES || BASE == BASE_BG));
+    constexpr bool LDS_TAB = lds_table<T, BASE, DERIV, FGM>();
     extern __shared__ double ltab[];   // LDS_TAB: [waves per block][NDF][NCP], sized at launch
     fill_log_table(tl);
     fill_exp_table(t2);
@@ -747,14 +762,14 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
                         strip_adjoint<T, L>(tab, px, py0, Gs, Gg, acc, t2);
                     continue;
                 }
-                if constexpr (DERIV && !FGM && (BASE == BASE_PLANES || BASE == BASE_BG)) {
+                if constexpr (!FGM && (DERIV ? (BASE == BASE_PLANES || BASE == BASE_BG) : (LDS_TAB && BASE == BASE_BG))) {
                     // Own values from pass A, then the pixel rows streamed as above.
-                    T fs[L], fg[L], fgd[KK ? L : 1];
+                    T fs[L], fg[L], fgd[KK != KK_NONE ? L : 1];
                     if constexpr (LDS_TAB)
-                        strip_values_staged<L, KK>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, t2,
+                        strip_values_staged<L, KK != KK_NONE>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, t2,
                                                    live, fgd);
                     else
-                        strip_values<T, L, KK, CULL_T>(tab, px, py0, fs, fg, t2, fgd, live);
+                        strip_values<T, L, KK != KK_NONE, CULL_T>(tab, px, py0, fs, fg, t2, fgd, live);
                     const double* xs_i = xs + im.pix_offset;
                     auto row_load = [&](int rr, double& x_, double& e_, double& v_) {
                         const size_t gi = (size_t)(r0 + rr) * im.W + c;
@@ -775,7 +790,7 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
                         double nx_ = 0.0, ne_ = 0.0, nv_ = 0.0;
                         if (kk + 1 < L) row_load(kk + 1 < nrow ? kk + 1 : 0, nx_, ne_, nv_);
                         T gs = zero, gg = zero;
-                        if constexpr (KK) {
+                        if constexpr (KK != KK_NONE) {
                             // own values for the closed-form Hessian pass that follows
                             if (a.fg_out && kk < nrow) {
                                 const size_t vi = (size_t)p.visit_off + (size_t)(r0 + kk - p.r0) * p.w + (c - p.c0);
@@ -794,21 +809,25 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
                                 E = ce_ + Es;
                                 V = cv_ + Vs;
                             }
-                            strip_pixel<T, true>(cx_, E, V, fs[kk], fg[kk], k, acc, gs, gg, tl);
-                            if constexpr (KK) pixel_kk(cx_, E, V, fs[kk], fg[kk], fgd[kk], k, kh);
+                            strip_pixel<T, DERIV>(cx_, E, V, fs[kk], fg[kk], k, acc, gs, gg, tl);
+                            if constexpr (KK != KK_NONE) pixel_kk(cx_, E, V, fs[kk], fg[kk], fgd[kk], k, kh);
                         }
-                        fs[kk] = gs;
-                        fg[kk] = gg;
+                        if constexpr (DERIV && KK != KK_PIXEL) {
+                            fs[kk] = gs;
+                            fg[kk] = gg;
+                        }
                         cx_ = nx_;
                         ce_ = ne_;
                         cv_ = nv_;
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if constexpr (LDS_TAB)
-                        strip_adjoint_staged<L>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, acc, t2,
-                                                live);
-                    else
-                        strip_adjoint<T, L, CULL_T>(tab, px, py0, fs, fg, acc, t2, live);
+                    if constexpr (DERIV && KK != KK_PIXEL) {
+                        if constexpr (LDS_TAB)
+                            strip_adjoint_staged<L>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, acc,
+                                                    t2, live);
+                        else
+                            strip_adjoint<T, L, CULL_T>(tab, px, py0, fs, fg, acc, t2, live);
+                    }
                     continue;
                 }
                 double x[L], Eb[L], Vb[L];
@@ -881,12 +900,13 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
                 if (DERIV) strip_adjoint<T, L>(tab, px, py0, fs, fg, acc, t2);
             }
             T* out = reinterpret_cast<T*>(partials) + (size_t)ii * NACC;
+            constexpr int NOUT = !DERIV ? A_VAL + 1 : KK == KK_PIXEL ? A_K4 + 1 : NACC;   // the sums this pass forms
 #pragma unroll
-            for (int f = 0; f < NACC; ++f) {
+            for (int f = 0; f < NOUT; ++f) {
                 const T s = wave_sum(acc[f]);
                 if (lane == 0) out[f] = s;
             }
-            if constexpr (KK) {
+            if constexpr (KK != KK_NONE) {
 #pragma unroll
                 for (int f = 0; f < NKK_USED; ++f) {
                     const double s = wave_sum(kh[f]);
@@ -945,7 +965,9 @@ __global__ void __launch_bounds__(256, (FGM && DERIV && std::is_same<T, double>:
 //   Sxx_Syy = Sxy_Sxy: wnu nu (N22 - d N20 - a N02 - 4b N11 + (ad + 2b^2) N00);
 //   Sxy_Syy: wnu nu (N13 - 3d N11 - 3b N02 + 3bd N00);   Syy_Syy: wnu nu (N04 - 6d N02 + 3d^2 N00)
 // (the expansions of the per-pixel formulas of hess_pixels), and for a star (weight Gs):
-// XX, XY, YY: N20 - a N00, N11 - b N00, N02 - d N00.  One pass over the components per strip
+// XX, XY, YY: N20 - a N00, N11 - b N00, N02 - d N00.  The same moments give the gradient's
+// position, frac_dev and shape sums (acc, A_UX .. A_SYY): wt (N10, N01), sgn N00 and wnu
+// (N20 - a N00, N11 - b N00, N02 - d N00); N10, N01 for a star.  One pass over the components per strip
 // (two exps per component), against one exp and about 55 operations per pixel and component
 // for the same terms pixel by pixel.
 enum HessStagedField { H_CX = 0, H_CY, H_LW, H_RDY, H_A, H_B, H_D, H_WT, H_WNU, H_SGN, H_NU, NDH };
@@ -979,7 +1001,7 @@ __device__ __forceinline__ void stage_hess(const double* __restrict__ tab, const
 
 template <int L>
 __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt, double px, double py0,
-                                                  const double* Gs, const double* Gg, double* H,
+                                                  const double* Gs, const double* Gg, double* H, double* acc,
                                                   const double* __restrict__ t2, uint64_t live) {
     constexpr double KC = 0.5 * (L - 1);
 #pragma unroll 1
@@ -1015,6 +1037,8 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             H[HG_XX] += fma(-a, U0, N20);
             H[HG_XY] += fma(-b, U0, N11);
             H[HG_YY] += fma(-d, U0, N02);
+            acc[A_UX - A_UX] += X10;
+            acc[A_UY - A_UX] += Y10;
         }
         auto gal = [&](const double* __restrict__ e) {
             const double a = e[H_A * NCP], b = e[H_B * NCP], d = e[H_D * NCP];
@@ -1073,6 +1097,12 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             H[HG_F_SXX] = fma(snu, e20, H[HG_F_SXX]);
             H[HG_F_SXY] = fma(snu, e11, H[HG_F_SXY]);
             H[HG_F_SYY] = fma(snu, e02, H[HG_F_SYY]);
+            acc[A_UX - A_UX] = fma(wt, N10, acc[A_UX - A_UX]);
+            acc[A_UY - A_UX] = fma(wt, N01, acc[A_UY - A_UX]);
+            acc[A_FDEV - A_UX] = fma(sg, N00, acc[A_FDEV - A_UX]);
+            acc[A_SXX - A_UX] = fma(wnu, e20, acc[A_SXX - A_UX]);
+            acc[A_SXY - A_UX] = fma(wnu, e11, acc[A_SXY - A_UX]);
+            acc[A_SYY - A_UX] = fma(wnu, e02, acc[A_SYY - A_UX]);
             const double x1 = fma(-3.0 * a, N10, N30);
             const double x2 = fma(-2.0 * b, N10, fma(-a, N01, N21));
             const double x3 = fma(-d, N10, fma(-2.0 * b, N01, N12));
@@ -1105,7 +1135,8 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
 // Second-derivative terms of the geometric block, one lane per strip: the row weights Gs, Gg
 // from the stored background and own profile values of each row, then hess_second_strip.
 // Writes hg[item] (geometric entries; the k-block entries zero), to which k_hess_geom then
-// adds the first-derivative products.  Items of sources outside a.active get zeros.
+// adds the first-derivative products, and the position, frac_dev and shape entries of
+// a.partials[item].  Items of sources outside a.active get zeros.
 // Three waves per SIMD (168 VGPRs, some spilled) rather than two (197 VGPRs): the waves wait
 // on each strip's row loads, and the third wave hides more of it (Newton iterations on 1024
 // sources 1.5% faster).
@@ -1146,9 +1177,11 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double H[NHG_GEO];
+        double H[NHG_GEO], acc[NACC - A_UX];
 #pragma unroll
         for (int f = 0; f < NHG_GEO; ++f) H[f] = 0.0;
+#pragma unroll
+        for (int f = 0; f < NACC - A_UX; ++f) acc[f] = 0.0;
         for (int q = lane; q < it.count; q += 64) {
             int c, r0, nrow;
             strip_geometry(p, it.start + q, L, c, r0, nrow);
@@ -1175,7 +1208,7 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
                 Gs[kk] = gs;
                 Gg[kk] = gg;
             }
-            hess_second_strip<L>(my, (double)c, (double)r0, Gs, Gg, H, t2, live);
+            hess_second_strip<L>(my, (double)c, (double)r0, Gs, Gg, H, acc, t2, live);
         }
 #pragma unroll
         for (int f = 0; f < NHG_GEO; ++f) {
@@ -1183,6 +1216,11 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
             if (lane == 0) out[f] = v;
         }
         if (lane >= NHG_GEO && lane < NHG) out[lane] = 0.0;
+#pragma unroll
+        for (int f = 0; f < NACC - A_UX; ++f) {
+            const double v = wave_sum(acc[f]);
+            if (lane == 0) a.partials[(size_t)ii * NACC + A_UX + f] = v;
+        }
         j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
     }
 }
@@ -1756,12 +1794,10 @@ hipError_t launch_render_strips(const Sel& sel, const Geometry& g, const double*
     return hipGetLastError();
 }
 
-template <class T, int BASE, bool DERIV, int L, bool FGM, bool KK>
+template <class T, int BASE, bool DERIV, int L, bool FGM, int KK>
 static void adjk(const AdjArgs& a, int grid, int wpb, hipStream_t st) {
     const Geometry& g = a.g;
-    constexpr bool lds_tab = DERIV && std::is_same<T, double>::value &&
-                             (FGM ? (BASE == BASE_PLANES || BASE == BASE_FG) : (BASE == BASE_PLANES || BASE == BASE_BG));
-    const size_t lds = lds_tab ? (size_t)wpb * NCP * NDF * sizeof(double) : 0;
+    const size_t lds = lds_table<T, BASE, DERIV, FGM>() ? (size_t)wpb * NCP * NDF * sizeof(double) : 0;
     hipLaunchKernelGGL((k_adjoint_strips<T, BASE, DERIV, L, FGM, KK>), dim3(grid), dim3(64 * wpb), lds, st, a,
                        g.items, g.pairs, g.images, g.nbr, g.x, a.E, a.V, a.bg, a.tab, a.coef, a.tab_val, a.coef_val,
                        a.active, a.fg, a.partials);
@@ -1778,17 +1814,18 @@ static hipError_t adjs(const AdjArgs& a, int grid, int wpb, hipStream_t st) {
     if (a.kk && !can_kk) return hipErrorInvalidValue;
     if constexpr (can_kk) {
         if (a.kk) {
-            adjk<T, BASE, DERIV, L, false, true>(a, grid, wpb, st);
+            if (a.kk_pixel) adjk<T, BASE, DERIV, L, false, KK_PIXEL>(a, grid, wpb, st);
+            else adjk<T, BASE, DERIV, L, false, KK_FULL>(a, grid, wpb, st);
             return hipSuccess;
         }
     }
     if constexpr (own_fg) {
         if (a.fg) {
-            adjk<T, BASE, DERIV, L, true, false>(a, grid, wpb, st);
+            adjk<T, BASE, DERIV, L, true, KK_NONE>(a, grid, wpb, st);
             return hipSuccess;
         }
     }
-    adjk<T, BASE, DERIV, L, false, false>(a, grid, wpb, st);
+    adjk<T, BASE, DERIV, L, false, KK_NONE>(a, grid, wpb, st);
     return hipSuccess;
 }
 
