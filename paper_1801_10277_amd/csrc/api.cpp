@@ -106,8 +106,6 @@ struct celeste_plan {
     unsigned long long* d_wcount = nullptr;   // [NLIVE_COUNTS] celeste_work_counts
     double* d_grad = nullptr;
     double* d_hess = nullptr;        // [S][npar][npar]
-    double* d_grad_trial = nullptr;  // gradient and Hessian at the Newton trial points
-    double* d_hess_trial = nullptr;
     uint8_t* d_accepted = nullptr;
     uint8_t* d_live = nullptr;
     double* d_gw = nullptr;      // [n_pairs][11] per-box gradient sums
@@ -879,21 +877,19 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.status = p->d_status;
         HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->wpb, p->rows, st));
     }
-    HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, p->d_kk, false, 0, p->d_gw, p->d_hw, p->d_status,
-                              st));
-    if (closed) {
-        HIPCHK(launch_pair_hess(pair, p->d_pairs, p->d_hg, p->d_hw, p->d_status, st));
-    } else {
+    HIPCHK(launch_pair_block(pair, p->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
+                             p->d_hw, active, p->d_status, st));
+    if (!closed) {
         for (int i = W_UX; i < NW; ++i) {
             if (i == W_FDEV) continue;
             CHK(prep(p, theta, pair, true, DIR_W, nullptr, i, st));
             CHK(adjoint(p, item, nullptr, true, base, true, st));
-            HIPCHK(launch_pair_reduce(pair, p->d_pairs, p->d_partials, nullptr, true, i, p->d_gw, p->d_hw,
-                                      p->d_status, st));
+            HIPCHK(launch_pair_block(pair, p->d_pairs, p->d_partials, nullptr, nullptr, true, i, p->d_gw, p->d_hw,
+                                     active, p->d_status, st));
         }
     }
-    HIPCHK(launch_assemble_hessian(src, p->geom(), p->d_patch_ptr, theta, p->d_gw, p->d_hw, hess, grad, active,
-                                   p->d_status, st));
+    HIPCHK(launch_assemble_hessian(src, p->geom(), p->d_patch_ptr, theta, p->d_coef1, p->d_gw, p->d_hw, hess, grad,
+                                   active, p->d_status, st));
     return CELESTE_OK;
 }
 
@@ -915,8 +911,6 @@ int newton_run(celeste_plan* p, double* theta, const Sel& src, const Sel& pair, 
     tr.theta = theta;
     tr.grad = p->d_grad;
     tr.hess = p->d_hess;
-    tr.grad_trial = p->d_grad_trial;
-    tr.hess_trial = p->d_hess_trial;
     tr.accepted = p->d_accepted;
     tr.live = p->d_live;
     tr.radius = radius;
@@ -941,7 +935,7 @@ int newton_run(celeste_plan* p, double* theta, const Sel& src, const Sel& pair, 
         HIPCHK(launch_tr_solve(tr, st));
         // the trial point of every source still stepping (d_live): its value; then, except
         // after the last step and for the sources whose step was accepted, its gradient and
-        // Hessian, which become the current ones (a rejected step keeps the point and with it
+        // Hessian in place of the current ones (a rejected step keeps the point and with it
         // the current gradient and Hessian)
         const bool more = it + 1 < n_steps;
         CHK(prep(p, p->d_theta_trial, pair, false, DIR_NONE, nullptr, 0, st));
@@ -949,11 +943,9 @@ int newton_run(celeste_plan* p, double* theta, const Sel& src, const Sel& pair, 
         CHK(finalize(p, p->d_theta_trial, src, p->d_live, false, DIR_NONE, nullptr, 0, false, p->d_elbo_trial,
                      nullptr, nullptr, 0, false, st));
         HIPCHK(launch_tr_update(tr, st));
-        if (more) {
-            CHK(hessian_from_intermediates(p, p->d_theta_trial, src, pair, item, BASE_BG, p->d_hess_trial,
-                                           p->d_grad_trial, st, p->d_accepted));
-            HIPCHK(launch_tr_adopt(tr, st));
-        }
+        if (more)
+            CHK(hessian_from_intermediates(p, p->d_theta_trial, src, pair, item, BASE_BG, p->d_hess, p->d_grad, st,
+                                           p->d_accepted));
     }
     return CELESTE_OK;
 }
@@ -1022,7 +1014,7 @@ void celeste_plan_destroy(celeste_plan* p) {
                     p->d_tile_sums, p->d_status, p->d_counter, p->d_grad, p->d_hess, p->d_theta_trial,
                     p->d_pred, p->d_elbo_cur, p->d_elbo_trial, p->d_radius, p->d_done, p->d_list_src,
                     p->d_list_pair, p->d_list_item, p->d_cls_items, p->d_pair_lgamma, p->d_fg, p->d_gw,
-                    p->d_hw, p->d_kk, p->d_hg, p->d_nu, p->d_grad_trial, p->d_hess_trial, p->d_accepted, p->d_live,
+                    p->d_hw, p->d_kk, p->d_hg, p->d_nu, p->d_accepted, p->d_live,
                     p->d_mix, p->d_scalar, p->d_tt_part, p->d_list_npair, p->d_list_nitem, p->d_wcount};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -1127,8 +1119,6 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     const size_t S = (size_t)p->n_src;
     A(dalloc(&p->d_grad, S * ROW, W));
     A(dalloc(&p->d_hess, S * NPK * NPK, W));
-    A(dalloc(&p->d_grad_trial, S * ROW, W));
-    A(dalloc(&p->d_hess_trial, S * NPK * NPK, W));
     A(dalloc(&p->d_accepted, S, W));
     A(dalloc(&p->d_live, S, W));
     A(dalloc(&p->d_gw, np * NACC, W));

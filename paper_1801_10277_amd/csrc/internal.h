@@ -253,21 +253,20 @@ hipError_t launch_live_counts(const Sel& sel, const Geometry& g, const double* t
 hipError_t launch_fill_u8_sel(uint8_t* p, const Sel& s, uint8_t v, hipStream_t st);
 hipError_t launch_fill_f64_sel(double* p, const Sel& s, double v, hipStream_t st);
 
-// Per-box sums of item partials: value parts into gw[pair][NACC] and, with kk, the k-block
-// hw[pair][0..3][0..3] (double pass), or the tangent parts of accumulators 1..10 into
-// hw[pair][dir][10] (tangent pass along a pair-intermediate direction).
-hipError_t launch_pair_reduce(const Sel& pairs, const PairDev* dpairs, const double* partials, const double* kk,
-                              bool tangent, int dir, double* gw, double* hw, const int* status, hipStream_t st);
-// Per-box sums of hg into the position and shape rows of hw[pair] (hw[pair][dir][f] =
-// c_f d2L / dw_dir dw_f, as the tangent passes give them).
-hipError_t launch_pair_hess(const Sel& pairs, const PairDev* dpairs, const double* hg, double* hw, const int* status,
-                            hipStream_t st);
-// 27x27 Hessians of the listed sources (hess by list position) from gw, hw and the KL.
+// Per-box sums of the item sums: the gradient's into gw[pair][NACC], the pixel-level (kk) and
+// closed-form (hg) Hessian sums, where given, as their rows of hw[pair][10][10] (hw[dir][f] =
+// c_f d2L / dw_dir dw_f); or, tangent, the tangent parts of accumulators 1..10 into
+// hw[pair][dir][10].  active (or null): only the boxes of the marked sources.
+hipError_t launch_pair_block(const Sel& pairs, const PairDev* dpairs, const double* partials, const double* kk,
+                             const double* hg, bool tangent, int dir, double* gw, double* hw, const uint8_t* active,
+                             const int* status, hipStream_t st);
+// Hessians of the listed sources (hess by list position) from gw, hw, the boxes' brightness
+// factors at theta (coef) and the KL.
 // grad (or null): also the gradient rows [S][ROW] of the listed sources.  active (or null):
 // only the marked sources.
 hipError_t launch_assemble_hessian(const Sel& srcs, const Geometry& g, const int32_t* patch_ptr,
-                                   const double* theta, const double* gw, const double* hw, double* hess,
-                                   double* grad, const uint8_t* active, const int* status, hipStream_t st);
+                                   const double* theta, const double* coef, const double* gw, const double* hw,
+                                   double* hess, double* grad, const uint8_t* active, const int* status, hipStream_t st);
 // out[s] = in[s] of the listed sources.
 hipError_t launch_copy_f64_sel(double* out, const double* in, const Sel& s, const int* status, hipStream_t st);
 
@@ -287,8 +286,6 @@ struct TrArgs {
     double* theta;             // [S][32] current point, updated by tr_update
     double* grad;              // [S][32] natural-space gradient at theta
     double* hess;              // [n][27][27] by list position
-    const double* grad_trial;  // [S][32] gradient at the trial point, or null
-    const double* hess_trial;  // [n][27][27] Hessian at the trial point, or null
     uint8_t* accepted;         // [S] set by tr_update: the trial point became the current one
     double* radius;            // [S]
     double* theta_trial;       // [S][32]
@@ -303,7 +300,5 @@ struct TrArgs {
 };
 hipError_t launch_tr_solve(const TrArgs& a, hipStream_t st);
 hipError_t launch_tr_update(const TrArgs& a, hipStream_t st);
-// Gradient and Hessian of the trial point become the current ones where it was accepted.
-hipError_t launch_tr_adopt(const TrArgs& a, hipStream_t st);
 
 }  // namespace cel

@@ -20,8 +20,9 @@
 //     Math. 11, 1968) and the subproblem in the eigenbasis, the hard case along the
 //     eigenvector of the smallest eigenvalue;
 //  5. trial point and predicted increase.
-// k_tr_update compares the actual and predicted increase and updates point and radius;
-// k_tr_adopt then takes over the trial point's gradient and Hessian where it was accepted.
+// k_tr_update compares the actual and predicted increase and updates point and radius; where
+// the trial point was accepted its gradient and Hessian are then formed in place of the
+// current ones.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -32,14 +33,6 @@ namespace cel {
 constexpr int NEM = NP + 2 * (NMIX - 1);   // unconstrained coordinates with the mixture: 41
 constexpr int QL_MAX_ITER = 60;   // QL iterations per eigenvalue before giving up
 constexpr double EPS_D = 2.220446049250313e-16;   // 2^-52
-
-// Value of v in lane i (i wave-uniform).
-__device__ inline double lane_get(double v, int i) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, i);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 
 // Wave-wide minimum and maximum (every lane receives the result).
 __device__ inline double wave_min(double v) {
@@ -341,19 +334,19 @@ __global__ void __launch_bounds__(64) k_tr_solve(TrArgs a) {
             if (!(w > 4.0 * EPS_D * fmax(fabs(lo_e), fabs(hi_e)) + 1e-300)) break;
             const double x = lo_e + w * ((double)(t + 1) / 65.0);
             int cnt = 0;
-            double q = lane_get(dv, 0) - x;
+            double q = lane_bcast(dv, 0) - x;
             if (q == 0.0) q = -1e-300;
             cnt += q < 0.0;
             for (int i = 1; i < M; ++i) {
-                const double e1 = lane_get(ev, i - 1);
-                q = lane_get(dv, i) - x - e1 * e1 / q;
+                const double e1 = lane_bcast(ev, i - 1);
+                q = lane_bcast(dv, i) - x - e1 * e1 / q;
                 if (q == 0.0) q = -1e-300;
                 cnt += q < 0.0;
             }
             const unsigned long long hit = __ballot(cnt >= 1);
             const int k = hit ? __ffsll((long long)hit) - 1 : 64;
-            const double nlo = k == 0 ? lo_e : lane_get(x, k - 1);
-            const double nhi = k < 64 ? lane_get(x, k) : hi_e;
+            const double nlo = k == 0 ? lo_e : lane_bcast(x, k - 1);
+            const double nhi = k < 64 ? lane_bcast(x, k) : hi_e;
             if (nlo == lo_e && nhi == hi_e) break;
             lo_e = nlo;
             hi_e = nhi;
@@ -368,11 +361,11 @@ __global__ void __launch_bounds__(64) k_tr_solve(TrArgs a) {
         bool pos = true;
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const double em1 = i > 0 ? lane_get(ev, i - 1) : 0.0;
-            const double den = lane_get(dv, i) + mu - em1 * cprev;
+            const double em1 = i > 0 ? lane_bcast(ev, i - 1) : 0.0;
+            const double den = lane_bcast(dv, i) + mu - em1 * cprev;
             pos = pos && den > 0.0;
             const double inv = 1.0 / den;
-            cprev = i < M - 1 ? lane_get(ev, i) * inv : 0.0;
+            cprev = i < M - 1 ? lane_bcast(ev, i) * inv : 0.0;
             cpv = t == i ? cprev : cpv;
             idv = t == i ? inv : idv;
         }
@@ -382,14 +375,14 @@ __global__ void __launch_bounds__(64) k_tr_solve(TrArgs a) {
         double rprev = 0.0, rpv = 0.0;
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const double em1 = i > 0 ? lane_get(ev, i - 1) : 0.0;
-            rprev = (lane_get(rhs, i) - em1 * rprev) * lane_get(idv, i);
+            const double em1 = i > 0 ? lane_bcast(ev, i - 1) : 0.0;
+            rprev = (lane_bcast(rhs, i) - em1 * rprev) * lane_bcast(idv, i);
             rpv = t == i ? rprev : rpv;
         }
         double ynext = rprev, yv = t == M - 1 ? rprev : 0.0;
 #pragma unroll
         for (int i = M - 2; i >= 0; --i) {
-            ynext = lane_get(rpv, i) - lane_get(cpv, i) * ynext;
+            ynext = lane_bcast(rpv, i) - lane_bcast(cpv, i) * ynext;
             yv = t == i ? ynext : yv;
         }
         return yv;
@@ -486,17 +479,17 @@ __global__ void __launch_bounds__(64) k_tr_solve(TrArgs a) {
                 converged = false;
                 break;
             }
-            const double el = lane_get(ev, l), dl = lane_get(dv, l);
-            double g = (lane_get(dv, l + 1) - dl) / (2.0 * el);
+            const double el = lane_bcast(ev, l), dl = lane_bcast(dv, l);
+            double g = (lane_bcast(dv, l + 1) - dl) / (2.0 * el);
             double r = hypot(g, 1.0);
-            g = lane_get(dv, m) - dl + el / (g + copysign(r, g));
+            g = lane_bcast(dv, m) - dl + el / (g + copysign(r, g));
             double sn = 1.0, cs = 1.0, p = 0.0;
             bool deflated = false;
             // row t of Z: entry zpos, rotated but not yet stored, is carried in zc
             int zpos = m;
             double zc = (t < M) ? B[t][m] : 0.0;
             for (int i = m - 1; i >= l; --i) {
-                const double ei = lane_get(ev, i);
+                const double ei = lane_bcast(ev, i);
                 const double f = sn * ei, b = cs * ei;
                 // r = hypot(f, g) and 1 / r: the reciprocal square root of f^2 + g^2 (hardware
                 // estimate, two Newton steps) where the squares stay far from overflow and
@@ -522,8 +515,8 @@ __global__ void __launch_bounds__(64) k_tr_solve(TrArgs a) {
                 }
                 sn = f * rinv;
                 cs = g * rinv;
-                g = lane_get(dv, i + 1) - p;
-                r = (lane_get(dv, i) - g) * sn + 2.0 * cs * b;
+                g = lane_bcast(dv, i + 1) - p;
+                r = (lane_bcast(dv, i) - g) * sn + 2.0 * cs * b;
                 p = sn * r;
                 dv = t == i + 1 ? g + p : dv;
                 g = cs * r - b;
@@ -655,25 +648,6 @@ hipError_t launch_tr_solve(const TrArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(k_tr_solve<NP>, dim3(a.srcs.n), dim3(64), 0, st, a);
     else
         return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-// One work-group per listed source.
-__global__ void __launch_bounds__(256) k_tr_adopt(TrArgs a) {
-    if (*a.status) return;
-    const int j = blockIdx.x;
-    const int s = sel_at(a.srcs, j);
-    if (!a.accepted[s]) return;
-    const int n2 = a.npar * a.npar;
-    const double* hs = a.hess_trial + (size_t)j * n2;
-    double* hd = a.hess + (size_t)j * n2;
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) hd[i] = hs[i];
-    if (threadIdx.x < ROW) a.grad[(size_t)s * ROW + threadIdx.x] = a.grad_trial[(size_t)s * ROW + threadIdx.x];
-}
-
-hipError_t launch_tr_adopt(const TrArgs& a, hipStream_t st) {
-    if (a.srcs.n <= 0 || !a.hess_trial || !a.grad_trial) return hipSuccess;
-    hipLaunchKernelGGL(k_tr_adopt, dim3(a.srcs.n), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
