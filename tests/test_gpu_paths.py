@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from conftest import FLOOR, REL
+from conftest import FLOOR, REL, newton_step_bound
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,26 @@ def test_source_kernels_over_passes_of_boxes(B, O, synth, epochs, mixture):
         assert np.all(np.abs(hv[s, :n] - href) <= REL * np.abs(href) + FLOOR * habs), s
         Href, Habs = O.source_hessian(P, s, with_abs=True)
         assert np.all(np.abs(H[1 - s] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
+
+
+@pytest.mark.parametrize("mixture", [False, True])
+@pytest.mark.parametrize("radius", [1e-6, 1e-2, 0.5, 40.0])
+def test_trust_region_step_at_small_and_large_radii(B, synth, mixture, radius):
+    """One Newton step from the smallest radii (the multiplier far above the spectrum) to one
+    that leaves the interior step inside: within the derived one-step bound of the oracle's."""
+    from oracle import newton as N
+    from oracle import oracle as O
+    O.build()
+    f = synth.tiny(S=4, n_bands=3, size=25, side=15, seed=331)
+    if mixture:
+        f = synth.with_color_mixture(f, seed=2)
+    plan = B.Plan(f)
+    for s in range(4):
+        say("trust region radius", radius, "mixture", mixture, "source", s)
+        th = device(f.theta)
+        rad = torch.full((4,), radius, dtype=torch.float64, device="cuda")
+        _, rad = plan.newton(th, [s], 1, radius=rad)
+        bound, row, _, R = newton_step_bound(N, f, f.theta, s, radius)
+        diff = np.abs(th.cpu().numpy()[s, :len(row)] - row)
+        assert np.all(diff <= bound), (s, float((diff / np.maximum(bound, 1e-300)).max()))
+        assert float(rad[s]) == R
