@@ -63,6 +63,7 @@ struct celeste_plan {
     std::vector<TileDev> tiles;
     std::vector<int32_t> tile_list;
     Consts consts{};
+    bool smooth = false;   // every PSF covariance has eigenvalues >= 2/3 px^2
     const double* d_x = nullptr;
     int n_cu = 256;
 
@@ -163,6 +164,7 @@ struct celeste_plan {
         g.nbr = d_nbr;
         g.x = d_x;
         g.consts = consts;
+        g.smooth = smooth ? 1 : 0;
         return g;
     }
     int64_t n_pairs() const { return (int64_t)pairs.size(); }
@@ -1048,6 +1050,12 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     p->n_pix = d->n_pix;
     p->d_x = d->x;
     p->images.assign(d->images, d->images + d->n_img);
+    p->smooth = true;
+    for (const celeste_image& im : p->images)
+        for (const double(&ps)[6] : im.psf) {
+            const double tr = ps[3] + ps[5], df = ps[3] - ps[5];
+            if (!(0.5 * (tr - std::sqrt(df * df + 4.0 * ps[4] * ps[4])) >= 2.0 / 3.0)) p->smooth = false;
+        }
     p->patch_ptr.assign(d->patch_ptr, d->patch_ptr + d->n_src + 1);
     std::memcpy(p->consts.exp_alpha, d->exp_alpha, sizeof(d->exp_alpha));
     std::memcpy(p->consts.exp_nu, d->exp_nu, sizeof(d->exp_nu));

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(PKG)
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libceleste.so")
 SOURCES = ["kernels.hip", "strips.hip", "tr.hip", "noalloc.hip", "api.cpp"]
-HEADERS = ["dual.h", "internal.h", "model.h"]
+HEADERS = ["dual.h", "internal.h", "model.h", "tables.h"]
 ARCH = os.environ.get("CELESTE_OFFLOAD_ARCH", "gfx950")
 
 

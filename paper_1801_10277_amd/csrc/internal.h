@@ -134,6 +134,7 @@ struct Geometry {
     const int32_t* nbr;
     const double* x;
     Consts consts;
+    int32_t smooth;            // every PSF covariance has eigenvalues >= 2/3 px^2 (strips.hip: row factors)
 };
 
 struct PrepArgs {

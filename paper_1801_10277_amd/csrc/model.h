@@ -4,6 +4,7 @@
 // the library's header.
 #pragma once
 #include "internal.h"
+#include "tables.h"
 
 namespace cel {
 
@@ -24,18 +25,13 @@ constexpr double LOG_2PI = 1.8378770664093454836;
 // entries: x = (256 k + j) ln2/256 + r, |r| <= ln2/512, so e^x = 2^k 2^(j/256) e^r and e^r is
 // the degree-4 Taylor polynomial (truncation r^5/120 < 3.8e-17 relative).  The reduction
 // x - n ln2/256 takes ln2/256 in two parts through fused multiply-adds.  The table
-// t2[j] = 2^(j/256) lives in LDS (fill_exp_table).  Accuracy within a few ulps of the
+// t2[j] = 2^(j/256) lives in LDS (load_tables).  Accuracy within a few ulps of the
 // correctly rounded result for arguments down to the underflow threshold; arguments must
 // be <= 709 (callers clamp) and not NaN.
 constexpr int EXP_TAB = 256;
 constexpr double INV_LN2_256 = 369.32993046757463228;      // 256 / ln 2
 constexpr double LN2_256_HI = 2.7076061740622862743e-03;    // ln 2 / 256 rounded
 constexpr double LN2_256_LO = 9.0587766165871076501e-20;    // ln 2 / 256 - LN2_256_HI
-
-__device__ __forceinline__ void fill_exp_table(double* t2) {
-    for (int j = threadIdx.x; j < EXP_TAB; j += blockDim.x) t2[j] = exp2((double)j * (1.0 / EXP_TAB));
-    __syncthreads();
-}
 
 __device__ __forceinline__ double fexp(double x, const double* __restrict__ t2) {
     const double n = rint(x * INV_LN2_256);
@@ -46,6 +42,35 @@ __device__ __forceinline__ double fexp(double x, const double* __restrict__ t2) 
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
     return ldexp(t2[ni & (EXP_TAB - 1)] * p, ni >> 8);
+}
+
+// fexp of N arguments, bitwise the same values, with the N table reads issued together
+// before the N polynomials: one after another, each read's latency stands in its
+// exponential's chain (the scheduler keeps that order for fewer live registers; the fences
+// keep it from going back to it).
+template <int N>
+__device__ __forceinline__ void fexps(const double* x, double* e, const double* __restrict__ t2) {
+    double r[N], tb[N], p[N];
+    int ni[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double n = rint(x[i] * INV_LN2_256);
+        r[i] = fma(-n, LN2_256_LO, fma(-n, LN2_256_HI, x[i]));
+        ni[i] = (int)n;
+        tb[i] = t2[ni[i] & (EXP_TAB - 1)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(r[i], 1.0 / 24.0, 1.0 / 6.0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(p[i], r[i], 0.5);
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(p[i], r[i], 1.0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(p[i], r[i], 1.0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = ldexp(tb[i] * p[i], ni[i] >> 8);
 }
 
 __device__ __forceinline__ dual fexp(dual x, const double* __restrict__ t2) {
@@ -59,16 +84,18 @@ __device__ __forceinline__ dual fexp(dual x, const double* __restrict__ t2) {
 // breakpoints (j = the top 7 fraction bits of y), f = y - F_j is exact, and
 // log x = m ln2 + log F_j + log1p(f / F_j) with |f / F_j| <= 1/256, log1p by its degree-6
 // Taylor polynomial (truncation < 2.1e-18).  tl[j] = (1 / F_j, log F_j) lives in LDS
-// (fill_log_table).  Relative error a few ulps away from x = 1; near x = 1 the error is a
+// (load_tables).  Relative error a few ulps away from x = 1; near x = 1 the error is a
 // few 1e-16 absolute (the m ln2 and log F_j terms cancel there).
 constexpr double LN2_HI = 6.93147180369123816490e-01;       // ln 2, leading 32 bits
 constexpr double LN2_LO = 1.90821492927058770002e-10;       // ln 2 - LN2_HI
 
-__device__ __forceinline__ void fill_log_table(double2* tl) {
-    for (int j = threadIdx.x; j < 128; j += blockDim.x) {
-        const double F = 0.5 + (j + 0.5) * (1.0 / 256.0);
-        tl[j] = make_double2(1.0 / F, log(F));
-    }
+// The exp table and, with tl, the log table into LDS.  (Computed block by block instead, they
+// cost a few hundred instructions per wave, several percent of a work item.)
+__device__ __forceinline__ void load_tables(double* t2, double2* tl) {
+    for (int j = threadIdx.x; j < EXP_TAB; j += blockDim.x) t2[j] = EXP2_TABLE[j];
+    if (tl)
+        for (int j = threadIdx.x; j < 128; j += blockDim.x) tl[j] = make_double2(LOG_TABLE[j][0], LOG_TABLE[j][1]);
+    __syncthreads();
 }
 
 __device__ __forceinline__ double flog(double x, const double2* __restrict__ tl) {
@@ -330,6 +357,55 @@ __device__ inline void wave_sums(double* v) {
 #pragma unroll
         for (int f = 0; f < N; ++f) v[f] += t[f];
     }
+}
+// Wave sums of N values at once, dealt to the lanes: with K = (N + 3) / 4, lane c < K of
+// 16-lane row r returns the sum of v[r K + c] (values past N count 0) and `f` receives
+// r K + c (-1 in the other lanes).  The halves, then the quarters, of the wave are exchanged
+// between pairs of values by the swap instructions, so the work halves with each of the first
+// two steps and nothing goes through LDS: 5 N / 4 + N exchanges of three instructions, against
+// 6 N of a shuffle's five and its latency for N butterflies.  Fixed order.
+template <int CTRL>
+__device__ __forceinline__ double row_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    unsigned int l0, l1, h0, h1;
+    if constexpr (HALF) {   // lanes 32..63 of a with lanes 0..31 of b
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned int)x, (unsigned int)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+        l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+    } else {                // the odd 16-lane rows of a with the even rows of b
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned int)x, (unsigned int)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+        l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+    }
+    return __longlong_as_double(((long long)h0 << 32) | l0) + __longlong_as_double(((long long)h1 << 32) | l1);
+}
+template <int N>
+__device__ __forceinline__ double wave_sums_dealt(const double* v, int lane, int& f) {
+    constexpr int K = (N + 3) / 4;
+    static_assert(K <= 16, "a row holds at most 16 sums");
+    double x[2 * K], r = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2 * K; ++i) x[i] = swap_add<true>(i < N ? v[i] : 0.0, i + 2 * K < N ? v[i + 2 * K] : 0.0);
+    const int c = lane & 15;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        double y = swap_add<false>(x[i], x[i + K]);
+        y = row_add<0x128>(y);   // row_ror:8, 4, 2, 1
+        y = row_add<0x124>(y);
+        y = row_add<0x122>(y);
+        y = row_add<0x121>(y);
+        r = c == i ? y : r;
+    }
+    f = (lane >> 4) * K + c;
+    if (c >= K || f >= N) f = -1;
+    return r;
 }
 // v[lane] in lanes below N (zero above): N wave-uniform values spread over the lanes, so
 // that one coalesced store by lanes 0..N-1 writes them all

@@ -220,6 +220,48 @@ __device__ __forceinline__ void stage_derived(const double* __restrict__ tab, do
     }
 }
 
+// Row factors.  About the strip's centre row (KC = (L - 1) / 2), a component's value in row k is
+// n_k = N0 r^k q_|k - KC| with r = exp(-(b dx + d dy_c)) the lane's row ratio at the centre,
+// N0 = n_c r^-KC and q_j+1/2 = exp(-d (j + 1/2)^2 / 2) the same for every lane: with the q in
+// LDS (q_1/2 .. q_15/2 per component, staged with the table) a row of the value pass takes two
+// operations per component (p *= r, f += q p) instead of the recurrence's three, and a row of
+// the adjoint four instead of five (strip_adjoint_q).  It needs r^15 and N0 within range:
+// for P_yy = d <= 1.5, (b dx + d dy_c)^2 <= d (quadratic form at the centre), so where
+// log r > 40 the exponent of N0 is below -40^2 / (2 d) - 40 KC < -800: N0 is exactly 0 and r may
+// be clamped there; r^15 then stays below e^600 and N0 below e^42.  A component whose value in
+// some row exceeds exp(-50) of its peak has log r < 24, so the terms are formed as exactly as
+// with the recurrence from the top row.  Every component covariance holds its PSF
+// component's, so d <= 1.5 everywhere when the PSF covariances' eigenvalues are at least
+// 2/3 px^2 (sigma >= 0.82 px): the plan tests that (Geometry::smooth), and plans with a
+// sharper PSF take the recurrence.
+constexpr double LOG_R_MAX = 40.0;
+constexpr int NQ = 8;   // row factors per component (L / 2 of them are used)
+
+// One wave writes the row factors of a box's components into its LDS slot [NCP][NQ] (0 for the
+// zero component): q_j+1 = q_j rho^(j+1), rho = exp(-d).
+__device__ __forceinline__ void stage_rows(const double* __restrict__ tab, double* myq, int lane,
+                                           const double* __restrict__ t2) {
+    if (lane > NCOMP) return;
+    double q[NQ];
+    if (lane < NCOMP) {
+        const double* e = tab + lane * CST;
+        const double rho = e[F_RDY];
+        double pw = rho;
+        q[0] = fexp(-0.125 * e[F_PYY], t2);
+#pragma unroll
+        for (int j = 1; j < NQ; ++j) {
+            q[j] = q[j - 1] * pw;
+            pw *= rho;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) q[j] = 0.0;
+    }
+    double* o = myq + (lane < NCOMP ? staged_slot(lane) : NPSF) * NQ;
+#pragma unroll
+    for (int j = 0; j < NQ; j += 2) *reinterpret_cast<double2*>(o + j) = make_double2(q[j], q[j + 1]);
+}
+
 // Components that are negligible on every pixel of a work item are left out of its strips.
 // The item's strips cover at most three rectangles of its box: the rest of its first band,
 // whole bands, the start of its last band.  For P = [[a, b], [b, d]] positive definite,
@@ -278,15 +320,31 @@ __device__ __forceinline__ void for_live_pairs(uint64_t live, int grp, F&& f) {
     }
 }
 
-// One galaxy component's rows and fold (strip_adjoint_staged), in its PSF group's frame.
+// Values n[0..1] and first row ratios rt[0..1] of two components (staged table entries e0, e1;
+// the fields of both staged layouts up to D_D coincide) in their PSF group's frame: both
+// entries' fields read together, then the four exponentials together.
+__device__ __forceinline__ void seed_pair(const double* __restrict__ e0, const double* __restrict__ e1, double h2x,
+                                          double mxy, double h2y, double mdx, double mdyh, double* n, double* rt,
+                                          const double* __restrict__ t2) {
+    const double a0 = e0[D_A * NCP], b0 = e0[D_B * NCP], d0 = e0[D_D * NCP], l0 = e0[D_LW * NCP];
+    const double a1 = e1[D_A * NCP], b1 = e1[D_B * NCP], d1 = e1[D_D * NCP], l1 = e1[D_LW * NCP];
+    __builtin_amdgcn_sched_barrier(0);
+    const double x[4] = {fma(a0, h2x, fma(b0, mxy, fma(d0, h2y, l0))), fma(a1, h2x, fma(b1, mxy, fma(d1, h2y, l1))),
+                         clamp_arg(fma(b0, mdx, d0 * mdyh)), clamp_arg(fma(b1, mdx, d1 * mdyh))};
+    double e[4];
+    fexps<4>(x, e, t2);
+    n[0] = e[0];
+    n[1] = e[1];
+    rt[0] = e[2];
+    rt[1] = e[3];
+}
+
+// One galaxy component's rows and fold (strip_adjoint_staged) from its value n and row ratio
+// rt at the strip's top row, in its PSF group's frame.
 template <int L>
-__device__ __forceinline__ void gal_adjoint_staged(const double* __restrict__ e, const double* Gg, double dx,
-                                                   double h2x, double mxy, double h2y, double mdx, double mdyh,
-                                                   double ev, double ev2, double e21, double* acc,
-                                                   const double* __restrict__ t2) {
+__device__ __forceinline__ void gal_adjoint_staged(const double* __restrict__ e, const double* Gg, double n, double rt,
+                                                   double dx, double ev, double ev2, double e21, double* acc) {
     const double a = e[D_A * NCP], b = e[D_B * NCP], d = e[D_D * NCP];
-    double n = fexp(fma(a, h2x, fma(b, mxy, fma(d, h2y, e[D_LW * NCP]))), t2);
-    double rt = fexp(clamp_arg(fma(b, mdx, d * mdyh)), t2);
     const double rdy = e[D_RDY * NCP];
     double A = 0.0, B = 0.0, C = 0.0;
 #pragma unroll
@@ -349,8 +407,10 @@ __device__ __forceinline__ void strip_adjoint_staged(const double* __restrict__ 
             acc[A_UY] = fma(b, X1, fma(d, M1, acc[A_UY]));
         }
         for_live_pairs(live, grp, [&](int s0, int s1) {
-            gal_adjoint_staged<L>(lt + s0, Gg, dx, h2x, mxy, h2y, mdx, mdyh, ev, ev2, e21, acc, t2);
-            gal_adjoint_staged<L>(lt + s1, Gg, dx, h2x, mxy, h2y, mdx, mdyh, ev, ev2, e21, acc, t2);
+            double n[2], rt[2];
+            seed_pair(lt + s0, lt + s1, h2x, mxy, h2y, mdx, mdyh, n, rt, t2);
+            gal_adjoint_staged<L>(lt + s0, Gg, n[0], rt[0], dx, ev, ev2, e21, acc);
+            gal_adjoint_staged<L>(lt + s1, Gg, n[1], rt[1], dx, ev, ev2, e21, acc);
         });
     }
 }
@@ -361,12 +421,8 @@ __device__ __forceinline__ void strip_adjoint_staged(const double* __restrict__ 
 // SGN: also fgd[k] = sum of the de Vaucouleurs minus the exponential components (d fg /
 // d frac_dev).
 template <int L, bool SGN>
-__device__ __forceinline__ void gal_values_staged(const double* __restrict__ e, double h2x, double mxy, double h2y,
-                                                  double mdx, double mdyh, double* fg, double* fgd,
-                                                  const double* __restrict__ t2) {
-    const double a = e[D_A * NCP], b = e[D_B * NCP], d = e[D_D * NCP];
-    double n = fexp(fma(a, h2x, fma(b, mxy, fma(d, h2y, e[D_LW * NCP]))), t2);
-    double rt = fexp(clamp_arg(fma(b, mdx, d * mdyh)), t2);
+__device__ __forceinline__ void gal_values_staged(const double* __restrict__ e, double n, double rt, double* fg,
+                                                  double* fgd) {
     const double rdy = e[D_RDY * NCP], wt = e[D_WT * NCP];
     const double sgn = SGN ? e[D_SGN * NCP] : 0.0;
 #pragma unroll
@@ -413,8 +469,184 @@ __device__ __forceinline__ void strip_values_staged(const double* __restrict__ l
             }
         }
         for_live_pairs(live, grp, [&](int s0, int s1) {
-            gal_values_staged<L, SGN>(lt + s0, h2x, mxy, h2y, mdx, mdyh, fg, fgd, t2);
-            gal_values_staged<L, SGN>(lt + s1, h2x, mxy, h2y, mdx, mdyh, fg, fgd, t2);
+            double n[2], rt[2];
+            seed_pair(lt + s0, lt + s1, h2x, mxy, h2y, mdx, mdyh, n, rt, t2);
+            gal_values_staged<L, SGN>(lt + s0, n[0], rt[0], fg, fgd);
+            gal_values_staged<L, SGN>(lt + s1, n[1], rt[1], fg, fgd);
+        });
+    }
+}
+
+// Row factors of a component from LDS.
+template <int L>
+__device__ __forceinline__ void load_rows(const double* __restrict__ qs, double* q) {
+#pragma unroll
+    for (int j = 0; j < L / 2; j += 2) {
+        const double2 v = *reinterpret_cast<const double2*>(qs + j);
+        q[j] = v.x;
+        q[j + 1] = v.y;
+    }
+}
+// Index of the factor of row k of L: rows k and L - 1 - k share one.
+template <int L>
+__device__ __forceinline__ constexpr int row_q(int k) {
+    return k < L / 2 ? L / 2 - 1 - k : k - L / 2;
+}
+
+// N0 and r of two components (the form of strip_values_q): the offsets are those of the centre row.
+template <int L>
+__device__ __forceinline__ void seed_pair_q(const double* __restrict__ e0, const double* __restrict__ e1, double h2x,
+                                            double mxy, double h2y, double mdx, double mdy, double* n, double* r,
+                                            const double* __restrict__ t2) {
+    constexpr double KC = 0.5 * (L - 1);
+    const double a0 = e0[D_A * NCP], b0 = e0[D_B * NCP], d0 = e0[D_D * NCP], l0 = e0[D_LW * NCP];
+    const double a1 = e1[D_A * NCP], b1 = e1[D_B * NCP], d1 = e1[D_D * NCP], l1 = e1[D_LW * NCP];
+    __builtin_amdgcn_sched_barrier(0);
+    const double g0 = fma(b0, mdx, d0 * mdy), g1 = fma(b1, mdx, d1 * mdy);   // log r
+    const double x[4] = {fma(-KC, g0, fma(a0, h2x, fma(b0, mxy, fma(d0, h2y, l0)))),
+                         fma(-KC, g1, fma(a1, h2x, fma(b1, mxy, fma(d1, h2y, l1)))), fmin(g0, LOG_R_MAX),
+                         fmin(g1, LOG_R_MAX)};
+    double e[4];
+    fexps<4>(x, e, t2);
+    n[0] = e[0];
+    n[1] = e[1];
+    r[0] = e[2];
+    r[1] = e[3];
+}
+template <int L>
+__device__ __forceinline__ void seed_one_q(const double* __restrict__ e, double h2x, double mxy, double h2y, double mdx,
+                                           double mdy, double& n, double& r, const double* __restrict__ t2) {
+    constexpr double KC = 0.5 * (L - 1);
+    const double a = e[D_A * NCP], b = e[D_B * NCP], d = e[D_D * NCP];
+    const double g = fma(b, mdx, d * mdy);
+    const double x[2] = {fma(-KC, g, fma(a, h2x, fma(b, mxy, fma(d, h2y, e[D_LW * NCP])))), fmin(g, LOG_R_MAX)};
+    double o[2];
+    fexps<2>(x, o, t2);
+    n = o[0];
+    r = o[1];
+}
+
+// strip_values_staged through the row factors (lq: the wave's [NCP][NQ]): the weight (de
+// Vaucouleurs / exponential share) goes into N0.  SGN: fg and fgd receive the sums of the de
+// Vaucouleurs and of the exponential components, of which the caller forms both profiles.
+template <int L, bool SGN = false>
+__device__ __forceinline__ void strip_values_q(const double* __restrict__ lt, const double* __restrict__ lq, double px,
+                                               double py0, double* fs, double* fg, const double* __restrict__ t2,
+                                               uint64_t live, double* fgd = nullptr) {
+    constexpr double KC = 0.5 * (L - 1);
+#pragma unroll
+    for (int k = 0; k < L; ++k) fs[k] = fg[k] = 0.0;
+    if constexpr (SGN) {
+#pragma unroll
+        for (int k = 0; k < L; ++k) fgd[k] = 0.0;
+    }
+    auto rows = [&](int slot, double p, double r, double* f) {
+        double q[NQ];
+        load_rows<L>(lq + slot * NQ, q);
+#pragma unroll
+        for (int k = 0; k < L; ++k) {
+            f[k] = fma(q[row_q<L>(k)], p, f[k]);
+            if (k + 1 < L) p *= r;
+        }
+    };
+#pragma unroll 1
+    for (int grp = 0; grp < NPSF; ++grp) {
+        const bool star = (live >> grp) & 1;
+        if (!star && !((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
+        const double* es = lt + grp;
+        const double dx = px - es[D_CX * NCP], dy = py0 + KC - es[D_CY * NCP];
+        const double h2x = -0.5 * (dx * dx), mxy = -(dx * dy), h2y = -0.5 * (dy * dy);
+        if (star) {
+            double n, r;
+            seed_one_q<L>(es, h2x, mxy, h2y, -dx, -dy, n, r, t2);
+            rows(grp, n, r, fs);
+        }
+        auto pair = [&](int s0, int s1, double* f) {
+            double n[2], r[2];
+            seed_pair_q<L>(lt + s0, lt + s1, h2x, mxy, h2y, -dx, -dy, n, r, t2);
+            rows(s0, SGN ? n[0] : n[0] * lt[s0 + D_WT * NCP], r[0], f);
+            rows(s1, SGN ? n[1] : n[1] * lt[s1 + D_WT * NCP], r[1], f);
+        };
+        if constexpr (SGN) {
+            constexpr uint64_t dev = ((1ull << NDEV) - 1) << NPSF;
+            for_live_pairs(live & (dev << (grp * NGAL_PER_PSF)), grp, [&](int s0, int s1) { pair(s0, s1, fg); });
+            for_live_pairs(live & ~(dev << (grp * NGAL_PER_PSF)), grp, [&](int s0, int s1) { pair(s0, s1, fgd); });
+        } else {
+            for_live_pairs(live, grp, [&](int s0, int s1) { pair(s0, s1, fg); });
+        }
+    }
+}
+
+// strip_adjoint_staged through the row factors: with c_k = G_k q_k the moments of t_k = G_k n_k
+// are those of the polynomial P(r) = sum c_k r^k, sum t_k = N0 P, sum t_k k = N0 r P',
+// sum t_k k (k - 1) = N0 r^2 P'', P and its derivatives by Horner's rule (one product and three
+// multiply-adds a row, two for a star, which needs P and P' only).
+template <int L>
+__device__ __forceinline__ void strip_adjoint_q(const double* __restrict__ lt, const double* __restrict__ lq, double px,
+                                                double py0, const double* Gs, const double* Gg, double* acc,
+                                                const double* __restrict__ t2, uint64_t live) {
+    constexpr double KC = 0.5 * (L - 1);
+#pragma unroll 1
+    for (int grp = 0; grp < NPSF; ++grp) {
+        const bool star = (live >> grp) & 1;
+        if (!star && !((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
+        const double* es = lt + grp;
+        const double dx = px - es[D_CX * NCP], dy = py0 - es[D_CY * NCP], dyc = dy + KC;
+        const double h2x = -0.5 * (dx * dx), mxy = -(dx * dyc), h2y = -0.5 * (dyc * dyc);
+        const double dy2 = dy * dy, dy21 = 2.0 * dy + 1.0;
+        if (star) {
+            double n, r, q[NQ];
+            seed_one_q<L>(es, h2x, mxy, h2y, -dx, -dyc, n, r, t2);
+            load_rows<L>(lq + grp * NQ, q);
+            double h1 = Gs[L - 1] * q[row_q<L>(L - 1)];
+            double h0 = fma(h1, r, Gs[L - 2] * q[row_q<L>(L - 2)]);
+#pragma unroll
+            for (int k = L - 3; k >= 0; --k) {
+                h1 = fma(h1, r, h0);
+                h0 = fma(h0, r, Gs[k] * q[row_q<L>(k)]);
+            }
+            const double a = es[D_A * NCP], b = es[D_B * NCP], d = es[D_D * NCP];
+            const double M0 = n * h0, M1 = fma(dy, M0, (n * r) * h1), X1 = dx * M0;
+            acc[A_UX] = fma(a, X1, fma(b, M1, acc[A_UX]));
+            acc[A_UY] = fma(b, X1, fma(d, M1, acc[A_UY]));
+        }
+        auto gal = [&](int slot, double n, double r) {
+            const double* e = lt + slot;
+            double q[NQ];
+            load_rows<L>(lq + slot * NQ, q);
+            double h2 = Gg[L - 1] * q[row_q<L>(L - 1)];
+            double h1 = fma(h2, r, Gg[L - 2] * q[row_q<L>(L - 2)]);   // h0 of the second step
+            double h0 = fma(h1, r, Gg[L - 3] * q[row_q<L>(L - 3)]);
+            h1 = fma(h2, r, h1);
+#pragma unroll
+            for (int k = L - 4; k >= 0; --k) {
+                h2 = fma(h2, r, h1);
+                h1 = fma(h1, r, h0);
+                h0 = fma(h0, r, Gg[k] * q[row_q<L>(k)]);
+            }
+            const double a = e[D_A * NCP], b = e[D_B * NCP], d = e[D_D * NCP];
+            const double nr = n * r, A = n * h0, m1 = nr * h1, m2 = (nr * r) * (h2 + h2);
+            const double M1 = fma(dy, A, m1), M2 = fma(dy2, A, fma(dy21, m1, m2));
+            const double X1 = dx * A, Y1 = dx * M1;
+            const double U = fma(a, X1, b * M1), Up = fma(b, X1, d * M1);
+            const double W = fma(a, Y1, b * M2), Wp = fma(b, Y1, d * M2);
+            const double dU = fma(dx, U, -A), dUp = dx * Up, Wm = Wp - A;
+            const double wt = e[D_WT * NCP], wnu = e[D_WNU * NCP];
+            const double wna = wnu * a, wnb = wnu * b, wnd = wnu * d;
+            acc[A_FDEV] = fma(e[D_SGN * NCP], A, acc[A_FDEV]);
+            acc[A_UX] = fma(wt, U, acc[A_UX]);
+            acc[A_UY] = fma(wt, Up, acc[A_UY]);
+            acc[A_SXX] = fma(wna, dU, fma(wnb, W, acc[A_SXX]));
+            acc[A_SXY] = fma(wnb, dU, fma(wnd, W, acc[A_SXY]));
+            acc[A_SYY] = fma(wnb, dUp, fma(wnd, Wm, acc[A_SYY]));
+        };
+        for_live_pairs(live, grp, [&](int s0, int s1) {
+            // one seed after the other: a pair's do not fit beside the row weights
+            double n, r;
+            seed_one_q<L>(lt + s0, h2x, mxy, h2y, -dx, -dyc, n, r, t2);
+            gal(s0, n, r);
+            seed_one_q<L>(lt + s1, h2x, mxy, h2y, -dx, -dyc, n, r, t2);
+            gal(s1, n, r);
         });
     }
 }
@@ -575,7 +807,7 @@ __global__ void __launch_bounds__(256) k_render_strips(Sel sel, const Item* __re
                                                        double* __restrict__ V, const int* status) {
     if (*status) return;
     __shared__ double t2[EXP_TAB];
-    fill_exp_table(t2);
+    load_tables(t2, nullptr);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
@@ -605,6 +837,145 @@ __global__ void __launch_bounds__(256) k_render_strips(Sel sel, const Item* __re
 }
 
 // ----------------------------------------------------------------------- adjoint
+// Doubles of LDS per wave: the staged table [NDF][NCP] and the row factors [NCP][NQ].
+constexpr int STAGED = NCP * NDF + NCP * NQ;
+
+// The value-gradient pass over stored own profile values (the hot path): one wave per work
+// item; per strip the pixel terms row by row (their row weights stay in registers), then the
+// adjoint of every live Gaussian.  What bounds it is a wave's own latency as much as its
+// instructions: without any Gaussian the pass still took 233 of 557 us on the 2000-source
+// field, the rows' loads (40 B a visit) being waited for one row after another and three waves
+// a SIMD not covering it.  So the rows are loaded RB at a time, the next RB while these are
+// worked off, the first two lots before the box's table is staged; the tables of the
+// elementary functions are read instead of computed; the eleven sums leave by the swap
+// exchanges of wave_sums_dealt.  Row weights, two lots of rows and the sums fill the 168
+// registers that three waves a SIMD allow.  2000-source field: 557 -> 535 us (four rows a lot
+// spill 32 registers: 549), one source 27.0 -> 25.5 us.
+template <int BASE, int L, bool ROWQ>
+__global__ void __launch_bounds__(256, 3) k_adjoint_stored(AdjArgs a, const Item* __restrict__ items,
+                                                           const PairDev* __restrict__ pairs,
+                                                           const celeste_image* __restrict__ images,
+                                                           const int32_t* __restrict__ nbr,
+                                                           const double* __restrict__ xs,
+                                                           const double* __restrict__ Ep,
+                                                           const double* __restrict__ Vp,
+                                                           const double* __restrict__ tabp,
+                                                           const double* __restrict__ coefp,
+                                                           const uint8_t* __restrict__ active,
+                                                           const double* __restrict__ fgm,
+                                                           double* __restrict__ partials) {
+    if (*a.status) return;
+    __shared__ double t2[EXP_TAB];
+    __shared__ double2 tl[128];
+    extern __shared__ double ltab[];   // [waves per block][STAGED], sized at launch
+    load_tables(t2, tl);
+    const int lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6;
+    const int nw = gridDim.x * wpb;
+    double* my = ltab + (threadIdx.x >> 6) * STAGED;
+    constexpr int RB = 2, NB = L / RB;   // rows per lot, lots
+    int j = a.dynamic ? next_item_s(a.counter, lane) : blockIdx.x * wpb + (threadIdx.x >> 6);
+    while (j < a.items.n) {
+        const int ii = __builtin_amdgcn_readfirstlane(sel_at(a.items, j));
+        const Item it = items[ii];
+        const PairDev p = pairs[it.pair];
+        if (!active || active[p.src]) {
+            const celeste_image& im = images[p.img];
+            const double* tab = tabp + (size_t)it.pair * NCOMP * CST;
+            // Row addresses as 32-bit byte offsets from wave-uniform bases (the image's planes,
+            // the box's stored values; plan creation bounds images below 2^29 pixels and boxes
+            // below 2^28 visits): one add and one select per row.
+            const char* xb = reinterpret_cast<const char*>(xs + im.pix_offset);
+            const char* eb = reinterpret_cast<const char*>(Ep + im.pix_offset);
+            const char* vb = reinterpret_cast<const char*>(Vp + im.pix_offset);
+            const char* fb = reinterpret_cast<const char*>(fgm + 2 * p.visit_off);
+            const uint32_t W8 = (uint32_t)im.W * 8u, w16 = (uint32_t)p.w * 16u;
+            int c = 0, r0 = 0, nrow = 0;
+            uint32_t go = 0, vo = 0;
+            double x_[2][RB], e_[2][RB], v_[2][RB], s_[2][RB], g_[2][RB];
+            // lot b of the current strip's rows (a row past the box: the strip's top row)
+            auto load = [&](int b) {
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    const int rr = b * RB + i, u = b & 1;
+                    const bool in = rr < nrow;
+                    const uint32_t gr = go + (in ? (uint32_t)rr * W8 : 0u);
+                    const uint32_t vr = vo + (in ? (uint32_t)rr * w16 : 0u);
+                    x_[u][i] = *reinterpret_cast<const double*>(xb + gr);
+                    if constexpr (BASE == BASE_PLANES) {
+                        e_[u][i] = *reinterpret_cast<const double*>(eb + gr);
+                        v_[u][i] = *reinterpret_cast<const double*>(vb + gr);
+                    }
+                    const double2 sg = *reinterpret_cast<const double2*>(fb + vr);
+                    s_[u][i] = sg.x;
+                    g_[u][i] = sg.y;
+                }
+            };
+            const double* kp = coefp + (size_t)it.pair * NCOEF;
+            const double k[NCOEF] = {kp[0], kp[1], kp[2], kp[3]};
+            double acc[NACC];
+#pragma unroll
+            for (int f = 0; f < NACC; ++f) acc[f] = 0.0;
+            uint64_t live = 0;
+            for (int q0 = 0; q0 < it.count; q0 += 64) {
+                // lanes without a strip take the last one's with every row masked
+                strip_geometry(p, it.start + min(q0 + lane, it.count - 1), L, c, r0, nrow);
+                if (q0 + lane >= it.count) nrow = 0;
+                go = (uint32_t)(r0 * im.W + c) * 8u;
+                vo = (uint32_t)((r0 - p.r0) * p.w + (c - p.c0)) * 16u;
+                load(0);
+                if (q0 == 0) {
+                    // the wave's previous item has finished reading its copy (in-order LDS)
+                    __builtin_amdgcn_wave_barrier();
+                    stage_derived(tab, my, lane);
+                    if constexpr (ROWQ) stage_rows(tab, my + NCP * NDF, lane, t2);
+                    live = item_live(tab, p, it, L, lane);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                }
+                if constexpr (NB > 1) load(1);
+                double Eb[L], Vb[L];
+                if constexpr (BASE == BASE_FG) strip_background_fg<L>(p, pairs, nbr, coefp, fgm, im, c, r0, Eb, Vb);
+                double Gs[L], Gg[L];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                    for (int i = 0; i < RB; ++i) {
+                        const int kk = b * RB + i, u = b & 1;
+                        double gs = 0.0, gg = 0.0;
+                        if (kk < nrow && x_[u][i] == x_[u][i]) {
+                            double E, V;
+                            if constexpr (BASE == BASE_PLANES) {
+                                E = e_[u][i];
+                                V = v_[u][i];
+                            } else {
+                                const double Es = k[C_K1] * s_[u][i] + k[C_K2] * g_[u][i];
+                                E = Eb[kk] + Es;
+                                V = Vb[kk] + (k[C_K3] * (s_[u][i] * s_[u][i]) + k[C_K4] * (g_[u][i] * g_[u][i]) -
+                                              Es * Es);
+                            }
+                            strip_pixel<double, true>(x_[u][i], E, V, s_[u][i], g_[u][i], k, acc, gs, gg, tl);
+                        }
+                        Gs[kk] = gs;
+                        Gg[kk] = gg;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (b + 2 < NB) load(b + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const double px = (double)c, py0 = (double)r0;
+                if constexpr (ROWQ) strip_adjoint_q<L>(my, my + NCP * NDF, px, py0, Gs, Gg, acc, t2, live);
+                else strip_adjoint_staged<L>(my, px, py0, Gs, Gg, acc, t2, live);
+            }
+            int f;
+            const double s = wave_sums_dealt<NACC>(acc, lane, f);
+            if (f >= 0) partials[(size_t)ii * NACC + f] = s;
+        }
+        j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
+    }
+}
+
 // KK (double passes over stored backgrounds only): also the brightness-factor and frac_dev
 // block of each box's intermediate Hessian, per item into a.kk, and the own profile values
 // into a.fg_out.  KK_FULL is the whole gradient pass; KK_PIXEL leaves pass B out (the
@@ -615,21 +986,18 @@ __global__ void __launch_bounds__(256) k_render_strips(Sel sel, const Item* __re
 // At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
 // plus accumulation registers and run one wave per SIMD; with the bound they spill a few
 // hundred bytes per lane and run 17% faster (the value variants fit without spilling).
-// Three for the value-gradient pass over stored own values (the hot path): it needs 191
-// VGPRs unbounded and 168 with the bound (two registers spilled).
 // Whether a pass reads each box's table from LDS: the double passes that evaluate Gaussians
 // and take the background from planes, stored backgrounds or stored values.
 template <class T, int BASE, bool DERIV, bool FGM>
 constexpr bool lds_table() {
-    if (!std::is_same<T, double>::value) return false;
-    if (FGM) return DERIV && (BASE == BASE_PLANES || BASE == BASE_FG);
+    if (!std::is_same<T, double>::value || FGM) return false;
     return BASE == BASE_BG || (DERIV && BASE == BASE_PLANES);
 }
 
 enum KKMode { KK_NONE = 0, KK_FULL = 1, KK_PIXEL = 2 };
 
-template <class T, int BASE, bool DERIV, int L, bool FGM, int KK>
-__global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV && FGM ? 3 : 2)) k_adjoint_strips(AdjArgs a, const Item* __restrict__ items,
+template <class T, int BASE, bool DERIV, int L, bool FGM, int KK, bool ROWQ>
+__global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item* __restrict__ items,
                                                         const PairDev* __restrict__ pairs,
                                                         const celeste_image* __restrict__ images,
                                                         const int32_t* __restrict__ nbr,
@@ -645,16 +1013,13 @@ __global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV 
     if (*a.status) return;
     __shared__ double t2[EXP_TAB];
     __shared__ double2 tl[128];
-    // The value-gradient pass over stored own values (the hot path) reads each box's table
-    // from LDS, staged by the wave at the start of each item in the derived form of
-    // strip_adjoint_staged: the per-component loads of the galaxy loop then wait on LDS
-    // instead of missing the scalar cache (38% of the scalar loads missed with the table read
-    // from global memory), the table leaves the scalar registers (no spills), and the
-    // coefficients every lane shares are formed once per box instead of once per strip.
+    // The double passes read each box's table from LDS, staged by the wave at the start of each
+    // item in the derived form of strip_adjoint_staged: the per-component loads of the galaxy
+    // loop then wait on LDS instead of missing the scalar cache (38% of the scalar loads missed
+    // with the table read from global memory), and the table leaves the scalar registers.
     constexpr bool LDS_TAB = lds_table<T, BASE, DERIV, FGM>();
-    extern __shared__ double ltab[];   // LDS_TAB: [waves per block][NDF][NCP], sized at launch
-    fill_log_table(tl);
-    fill_exp_table(t2);
+    extern __shared__ double ltab[];   // LDS_TAB: [waves per block][STAGED], sized at launch
+    load_tables(t2, tl);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
@@ -670,12 +1035,15 @@ __global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV 
             // dual passes (HVP, Hessian tangents) read the table directly; they cull too
             constexpr bool CULL_T = !LDS_TAB && std::is_same<T, dual>::value;
             uint64_t live = 0;
+            const double* lt = ltab + (threadIdx.x >> 6) * STAGED;
+            const double* lq = lt + NCP * NDF;
             if constexpr (CULL_T) live = item_live(tab, p, it, L, lane);
             if constexpr (LDS_TAB) {
                 // the wave's previous item has finished reading its copy (in-order LDS)
-                double* my = ltab + (threadIdx.x >> 6) * (NCP * NDF);
+                double* my = ltab + (threadIdx.x >> 6) * STAGED;
                 __builtin_amdgcn_wave_barrier();
                 stage_derived(reinterpret_cast<const double*>(tab), my, lane);
+                if constexpr (ROWQ) stage_rows(reinterpret_cast<const double*>(tab), my + NCP * NDF, lane, t2);
                 live = item_live(reinterpret_cast<const double*>(tab), p, it, L, lane);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -693,82 +1061,25 @@ __global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV 
                 int c, r0, nrow;
                 strip_geometry(p, it.start + q, L, c, r0, nrow);
                 const double px = (double)c, py0 = (double)r0;
-                if constexpr (FGM && DERIV && (BASE == BASE_PLANES || BASE == BASE_FG)) {
-                    // Rows streamed one at a time, the next row's loads in flight, so that only
-                    // the row weights (and for BASE_FG the neighbours' background) stay live
-                    // into pass B.
-                    double Eb[L], Vb[L];
-                    if constexpr (BASE == BASE_FG)
-                        strip_background_fg<L>(p, pairs, nbr, coefv, fgm, im, c, r0, Eb, Vb);
-                    // Row addresses as 32-bit byte offsets from wave-uniform bases (the image's
-                    // planes, the box's stored values; plan creation bounds images below 2^29
-                    // pixels and boxes below 2^28 visits): one add and one select per row.
-                    const char* xb = reinterpret_cast<const char*>(xs + im.pix_offset);
-                    const char* eb = reinterpret_cast<const char*>(Ep + im.pix_offset);
-                    const char* vb = reinterpret_cast<const char*>(Vp + im.pix_offset);
-                    const char* fb = reinterpret_cast<const char*>(fgm + 2 * p.visit_off);
-                    const uint32_t W8 = (uint32_t)im.W * 8u, w16 = (uint32_t)p.w * 16u;
-                    const uint32_t go = (uint32_t)(r0 * im.W + c) * 8u;
-                    const uint32_t vo = (uint32_t)((r0 - p.r0) * p.w + (c - p.c0)) * 16u;
-                    // row rr of the strip if `in`, else its top row (a row past the box)
-                    auto row_load = [&](int rr, bool in, double& x_, double& e_, double& v_, double& s_,
-                                        double& g_) {
-                        const uint32_t gr = go + (in ? (uint32_t)rr * W8 : 0u);
-                        const uint32_t vr = vo + (in ? (uint32_t)rr * w16 : 0u);
-                        x_ = *reinterpret_cast<const double*>(xb + gr);
-                        if constexpr (BASE == BASE_PLANES) {
-                            e_ = *reinterpret_cast<const double*>(eb + gr);
-                            v_ = *reinterpret_cast<const double*>(vb + gr);
-                        }
-                        const double2 sg = *reinterpret_cast<const double2*>(fb + vr);
-                        s_ = sg.x;
-                        g_ = sg.y;
-                    };
-                    T Gs[L], Gg[L];
-                    double cx_, ce_ = 0.0, cv_ = 0.0, cs_, cg_;
-                    row_load(0, true, cx_, ce_, cv_, cs_, cg_);
-#pragma unroll
-                    for (int kk = 0; kk < L; ++kk) {
-                        double nx_ = 0.0, ne_ = 0.0, nv_ = 0.0, ns_ = 0.0, ng_ = 0.0;
-                        if (kk + 1 < L) row_load(kk + 1, kk + 1 < nrow, nx_, ne_, nv_, ns_, ng_);
-                        T gs = zero, gg = zero;
-                        if (kk < nrow && cx_ == cx_) {
-                            const T fsk = scalar_traits<T>::make(cs_, 0.0), fgk = scalar_traits<T>::make(cg_, 0.0);
-                            T E, V;
-                            if constexpr (BASE == BASE_PLANES) {
-                                E = scalar_traits<T>::make(ce_, 0.0);
-                                V = scalar_traits<T>::make(cv_, 0.0);
-                            } else {
-                                const T Es = k[C_K1] * fsk + k[C_K2] * fgk;
-                                const T Vs = k[C_K3] * (fsk * fsk) + k[C_K4] * (fgk * fgk) - Es * Es;
-                                E = Eb[kk] + Es;
-                                V = Vb[kk] + Vs;
-                            }
-                            strip_pixel<T, true>(cx_, E, V, fsk, fgk, k, acc, gs, gg, tl);
-                        }
-                        Gs[kk] = gs;
-                        Gg[kk] = gg;
-                        cx_ = nx_;
-                        ce_ = ne_;
-                        cv_ = nv_;
-                        cs_ = ns_;
-                        cg_ = ng_;
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if constexpr (LDS_TAB)
-                        strip_adjoint_staged<L>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, Gs, Gg,
-                                                acc, t2, live);
-                    else
-                        strip_adjoint<T, L>(tab, px, py0, Gs, Gg, acc, t2);
-                    continue;
-                }
                 if constexpr (!FGM && (DERIV ? (BASE == BASE_PLANES || BASE == BASE_BG) : (LDS_TAB && BASE == BASE_BG))) {
                     // Own values from pass A, then the pixel rows streamed as above.
                     T fs[L], fg[L], fgd[KK != KK_NONE ? L : 1];
-                    if constexpr (LDS_TAB)
-                        strip_values_staged<L, KK != KK_NONE>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, t2,
-                                                   live, fgd);
-                    else
+                    if constexpr (LDS_TAB) {
+                        if constexpr (ROWQ) {
+                            strip_values_q<L, KK != KK_NONE>(lt, lq, px, py0, fs, fg, t2, live, fgd);
+                            if constexpr (KK != KK_NONE) {
+                                const double fdev = lt[NPSF + 1 + D_WT * NCP];   // a de Vaucouleurs component's weight
+#pragma unroll
+                                for (int kk = 0; kk < L; ++kk) {
+                                    const double dv = fg[kk], ex = fgd[kk];
+                                    fg[kk] = fma(fdev, dv, (1.0 - fdev) * ex);
+                                    fgd[kk] = dv - ex;
+                                }
+                            }
+                        } else {
+                            strip_values_staged<L, KK != KK_NONE>(lt, px, py0, fs, fg, t2, live, fgd);
+                        }
+                    } else
                         strip_values<T, L, KK != KK_NONE, CULL_T>(tab, px, py0, fs, fg, t2, fgd, live);
                     const double* xs_i = xs + im.pix_offset;
                     auto row_load = [&](int rr, double& x_, double& e_, double& v_) {
@@ -822,10 +1133,10 @@ __global__ void __launch_bounds__(256, (std::is_same<T, double>::value && DERIV 
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr (DERIV && KK != KK_PIXEL) {
-                        if constexpr (LDS_TAB)
-                            strip_adjoint_staged<L>(ltab + (threadIdx.x >> 6) * (NCP * NDF), px, py0, fs, fg, acc,
-                                                    t2, live);
-                        else
+                        if constexpr (LDS_TAB) {
+                            if constexpr (ROWQ) strip_adjoint_q<L>(lt, lq, px, py0, fs, fg, acc, t2, live);
+                            else strip_adjoint_staged<L>(lt, px, py0, fs, fg, acc, t2, live);
+                        } else
                             strip_adjoint<T, L, CULL_T>(tab, px, py0, fs, fg, acc, t2, live);
                     }
                     continue;
@@ -1152,7 +1463,7 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
     if (*a.status) return;
     __shared__ double t2[EXP_TAB];
     extern __shared__ double ltab[];   // [waves per block][NDH][NCP], sized at launch
-    fill_exp_table(t2);
+    load_tables(t2, nullptr);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
@@ -1251,7 +1562,7 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
     if (*a.status) return;
     __shared__ double t2[EXP_TAB];
     extern __shared__ double ltab[];   // [waves per block][NDH][NCP], sized at launch
-    fill_exp_table(t2);
+    load_tables(t2, nullptr);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
@@ -1321,10 +1632,8 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
                         }
                     }
                 }
-                auto gal = [&](const double* __restrict__ e) {
+                auto gal = [&](const double* __restrict__ e, double n, double rt) {
                     const double a = e[H_A * NCP], b = e[H_B * NCP], d = e[H_D * NCP];
-                    double n = fexp(fma(a, h2x, fma(b, mxy, fma(d, h2y, e[H_LW * NCP]))), t2);
-                    double rt = fexp(clamp_arg(fma(b, mdx, d * mdyh)), t2);
                     const double rdy = e[H_RDY * NCP];
                     const double wt = e[H_WT * NCP], sg = e[H_SGN * NCP], wnu = e[H_WNU * NCP];
                     const double zx0 = fma(a, dx, b * dy), zy0 = fma(b, dx, d * dy);
@@ -1345,8 +1654,10 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
                     }
                 };
                 for_live_pairs(live, grp, [&](int s0, int s1) {
-                    gal(my + s0);
-                    gal(my + s1);
+                    double n[2], rt[2];
+                    seed_pair(my + s0, my + s1, h2x, mxy, h2y, mdx, mdyh, n, rt, t2);
+                    gal(my + s0, n[0], rt[0]);
+                    gal(my + s1, n[1], rt[1]);
                 });
             }
             // products of first derivatives and the k-block entries, row by row (the pixel
@@ -1420,7 +1731,7 @@ __global__ void __launch_bounds__(256) k_background_strips(BgArgs a, const Item*
                                                            double* __restrict__ bg) {
     if (*a.status) return;
     __shared__ double t2[EXP_TAB];
-    fill_exp_table(t2);
+    load_tables(t2, nullptr);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
@@ -1505,18 +1816,18 @@ __global__ void __launch_bounds__(256) k_pair_lgamma(const PairDev* __restrict__
 // Like the fused adjoint, the wave stages each item's box table into LDS and takes the seeds
 // in the PSF groups' centre frames: the table read through scalar loads had the waves
 // waiting on the scalar cache (render 0.488 -> 0.460 ms on the 2000-source field).
-template <int L>
+template <int L, bool ROWQ>
 __global__ void __launch_bounds__(256) k_strip_fg(Sel sel, const Item* __restrict__ items,
                                                   const PairDev* __restrict__ pairs, const double* __restrict__ tab,
                                                   double* __restrict__ fgm, const int* status) {
     if (*status) return;
     __shared__ double t2[EXP_TAB];
-    extern __shared__ double ltab[];   // [waves per block][NDF][NCP], sized at launch
-    fill_exp_table(t2);
+    extern __shared__ double ltab[];   // [waves per block][STAGED], sized at launch
+    load_tables(t2, nullptr);
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int nw = gridDim.x * wpb;
-    double* my = ltab + (threadIdx.x >> 6) * (NCP * NDF);
+    double* my = ltab + (threadIdx.x >> 6) * STAGED;
     for (int j = blockIdx.x * wpb + (threadIdx.x >> 6); j < sel.n; j += nw) {
         const int ii = __builtin_amdgcn_readfirstlane(sel_at(sel, j));
         const Item it = items[ii];
@@ -1524,6 +1835,7 @@ __global__ void __launch_bounds__(256) k_strip_fg(Sel sel, const Item* __restric
         const double* tb = tab + (size_t)it.pair * NCOMP * CST;
         __builtin_amdgcn_wave_barrier();
         stage_derived(tb, my, lane);
+        if constexpr (ROWQ) stage_rows(tb, my + NCP * NDF, lane, t2);
         const uint64_t live = item_live(tb, p, it, L, lane);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1532,7 +1844,8 @@ __global__ void __launch_bounds__(256) k_strip_fg(Sel sel, const Item* __restric
             int c, r0, nrow;
             strip_geometry(p, it.start + q, L, c, r0, nrow);
             double fs[L], fg[L];
-            strip_values_staged<L>(my, (double)c, (double)r0, fs, fg, t2, live);
+            if constexpr (ROWQ) strip_values_q<L>(my, my + NCP * NDF, (double)c, (double)r0, fs, fg, t2, live);
+            else strip_values_staged<L>(my, (double)c, (double)r0, fs, fg, t2, live);
 #pragma unroll
             for (int k = 0; k < L; ++k) {
                 if (k >= nrow) break;
@@ -1698,8 +2011,7 @@ __global__ void __launch_bounds__(256) k_debug_math(int fn, const double* __rest
                                                     int n) {
     __shared__ double t2[EXP_TAB];
     __shared__ double2 tl[128];
-    fill_log_table(tl);
-    fill_exp_table(t2);
+    load_tables(t2, tl);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     y[i] = fn == 0 ? fexp(x[i], t2) : fn == 1 ? flog(x[i], tl) : frcp(x[i]);
@@ -1733,14 +2045,22 @@ hipError_t launch_strip_fg(const Sel& sel, const Geometry& g, const double* tab,
     const int need = (sel.n + wpb - 1) / wpb;
     if (grid > need) grid = need;
     if (grid < 1) grid = 1;
-    if (L == 8)
-        hipLaunchKernelGGL(k_strip_fg<8>, dim3(grid), dim3(64 * wpb), (size_t)wpb * NCP * NDF * sizeof(double), st, sel, g.items, g.pairs, tab, fg, status);
-    else if (L == 4)
-        hipLaunchKernelGGL(k_strip_fg<4>, dim3(grid), dim3(64 * wpb), (size_t)wpb * NCP * NDF * sizeof(double), st, sel, g.items, g.pairs, tab, fg, status);
-    else if (L == 16)
-        hipLaunchKernelGGL(k_strip_fg<16>, dim3(grid), dim3(64 * wpb), (size_t)wpb * NCP * NDF * sizeof(double), st, sel, g.items, g.pairs, tab, fg, status);
-    else
+#define CEL_FG(LL, RQ)                                                                                          \
+    hipLaunchKernelGGL((k_strip_fg<LL, RQ>), dim3(grid), dim3(64 * wpb), (size_t)wpb * STAGED * sizeof(double), st, \
+                       sel, g.items, g.pairs, tab, fg, status)
+    if (L == 8) {
+        if (g.smooth) CEL_FG(8, true);
+        else CEL_FG(8, false);
+    } else if (L == 4) {
+        if (g.smooth) CEL_FG(4, true);
+        else CEL_FG(4, false);
+    } else if (L == 16) {
+        if (g.smooth) CEL_FG(16, true);
+        else CEL_FG(16, false);
+    } else {
         return hipErrorInvalidValue;
+    }
+#undef CEL_FG
     return hipGetLastError();
 }
 
@@ -1794,11 +2114,18 @@ hipError_t launch_render_strips(const Sel& sel, const Geometry& g, const double*
     return hipGetLastError();
 }
 
-template <class T, int BASE, bool DERIV, int L, bool FGM, int KK>
+template <class T, int BASE, bool DERIV, int L, bool FGM, int KK, bool ROWQ = false>
 static void adjk(const AdjArgs& a, int grid, int wpb, hipStream_t st) {
     const Geometry& g = a.g;
-    const size_t lds = lds_table<T, BASE, DERIV, FGM>() ? (size_t)wpb * NCP * NDF * sizeof(double) : 0;
-    hipLaunchKernelGGL((k_adjoint_strips<T, BASE, DERIV, L, FGM, KK>), dim3(grid), dim3(64 * wpb), lds, st, a,
+    // row factors where the pass reads the staged table and the plan's PSFs allow them
+    if constexpr (!ROWQ && lds_table<T, BASE, DERIV, FGM>()) {
+        if (g.smooth) {
+            adjk<T, BASE, DERIV, L, FGM, KK, true>(a, grid, wpb, st);
+            return;
+        }
+    }
+    const size_t lds = lds_table<T, BASE, DERIV, FGM>() ? (size_t)wpb * STAGED * sizeof(double) : 0;
+    hipLaunchKernelGGL((k_adjoint_strips<T, BASE, DERIV, L, FGM, KK, ROWQ>), dim3(grid), dim3(64 * wpb), lds, st, a,
                        g.items, g.pairs, g.images, g.nbr, g.x, a.E, a.V, a.bg, a.tab, a.coef, a.tab_val, a.coef_val,
                        a.active, a.fg, a.partials);
 }
@@ -1821,7 +2148,18 @@ static hipError_t adjs(const AdjArgs& a, int grid, int wpb, hipStream_t st) {
     }
     if constexpr (own_fg) {
         if (a.fg) {
-            adjk<T, BASE, DERIV, L, true, KK_NONE>(a, grid, wpb, st);
+            if constexpr (DERIV) {
+                const Geometry& g = a.g;
+                const size_t lds = (size_t)wpb * STAGED * sizeof(double);
+#define CEL_ADJ(RQ)                                                                                                    \
+    hipLaunchKernelGGL((k_adjoint_stored<BASE, L, RQ>), dim3(grid), dim3(64 * wpb), lds, st, a, g.items, g.pairs,      \
+                       g.images, g.nbr, g.x, a.E, a.V, a.tab, a.coef, a.active, a.fg, a.partials)
+                if (g.smooth) CEL_ADJ(true);
+                else CEL_ADJ(false);
+#undef CEL_ADJ
+            } else {
+                adjk<T, BASE, DERIV, L, true, KK_NONE>(a, grid, wpb, st);
+            }
             return hipSuccess;
         }
     }

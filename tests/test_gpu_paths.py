@@ -101,3 +101,29 @@ def test_trust_region_step_at_small_and_large_radii(B, synth, mixture, radius):
         diff = np.abs(th.cpu().numpy()[s, :len(row)] - row)
         assert np.all(diff <= bound), (s, float((diff / np.maximum(bound, 1e-300)).max()))
         assert float(rad[s]) == R
+
+
+@pytest.mark.parametrize("rows", [4, 8, 16])
+@pytest.mark.parametrize("eig", [(0.66, 0.66), (0.667, 0.667), (0.667, 4.0), (9.0, 9.0)])
+def test_row_factors_at_the_psf_limit(B, O, synth, eig, rows):
+    """ELBO, gradient, total ELBO and dense Hessian with PSF eigenvalues just below 2/3 px^2
+    (row-ratio recurrence), just above it (row factors at their sharpest, also rotated by 45
+    degrees) and far above, on boxes that reach tens of widths from the centre."""
+    f = synth.tiny(S=3, n_bands=2, size=71, side=61, seed=347)
+    a, b = eig
+    f.img_psf[:, :, 3] = f.img_psf[:, :, 5] = 0.5 * (a + b)
+    f.img_psf[:, :, 4] = 0.5 * (b - a)
+    plan, P = B.Plan(f), O.Problem(f)
+    plan.set_launch(strip_rows=rows)
+    th = device(f.theta)
+    say("row factors eig", eig, "rows", rows)
+    e, g = (t.cpu().numpy() for t in plan.elbo_grad(th))
+    H = plan.hessian(th, [0, 1, 2]).cpu().numpy()
+    np.testing.assert_allclose(float(plan.total_elbo(th)[0]), O.total_elbo(P), rtol=1e-11)
+    for s in range(3):
+        val, gref, gabs = O.source_grad(P, s)
+        ref = val[0] + val[1]
+        assert abs(e[s] - ref) <= REL * abs(ref) + FLOOR * abs(val[2]), s
+        assert np.all(np.abs(g[s, :27] - gref) <= REL * np.abs(gref) + FLOOR * gabs), s
+        Href, Habs = O.source_hessian(P, s, with_abs=True)
+        assert np.all(np.abs(H[s] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
