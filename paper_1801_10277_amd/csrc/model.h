@@ -344,20 +344,6 @@ __device__ inline double lane_bcast(double v, int i) {
 }
 __device__ inline dual lane_bcast(dual v, int i) { return mkd(lane_bcast(v.v, i), lane_bcast(v.t, i)); }
 
-// Wave sums of N values at once, each by the butterfly of wave_sum (so bitwise the same
-// sums): the N shuffles of a step are issued together and their latencies overlap, where
-// N calls of wave_sum would wait on each in turn.
-template <int N>
-__device__ inline void wave_sums(double* v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        double t[N];
-#pragma unroll
-        for (int f = 0; f < N; ++f) t[f] = __shfl_xor(v[f], o, 64);
-#pragma unroll
-        for (int f = 0; f < N; ++f) v[f] += t[f];
-    }
-}
 // Wave sums of N values at once, dealt to the lanes: with K = (N + 3) / 4, lane c < K of
 // 16-lane row r returns the sum of v[r K + c] (values past N count 0) and `f` receives
 // r K + c (-1 in the other lanes).  The halves, then the quarters, of the wave are exchanged
@@ -407,14 +393,4 @@ __device__ __forceinline__ double wave_sums_dealt(const double* v, int lane, int
     if (c >= K || f >= N) f = -1;
     return r;
 }
-// v[lane] in lanes below N (zero above): N wave-uniform values spread over the lanes, so
-// that one coalesced store by lanes 0..N-1 writes them all
-template <int N>
-__device__ inline double lane_pick(const double* v, int lane) {
-    double m = 0.0;
-#pragma unroll
-    for (int f = 0; f < N; ++f) m = lane == f ? v[f] : m;
-    return m;
-}
-
 }  // namespace cel

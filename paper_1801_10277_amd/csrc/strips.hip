@@ -982,7 +982,8 @@ __global__ void __launch_bounds__(256, 3) k_adjoint_stored(AdjArgs a, const Item
 // position, frac_dev and shape sums of the gradient come from the row moments that
 // k_hess_second takes anyway), so it holds no row weights and needs no second evaluation of
 // the Gaussians: on 1024 sources (1.6e7 visits) 618 -> 376 us a pass (bounded to three waves
-// per SIMD it spills 71 VGPRs and takes as long), k_hess_second 560 -> 600 us.
+// per SIMD it spills 71 VGPRs and takes as long), k_hess_second 560 -> 600 us; with the row
+// factors and the dealt sums the pass takes 311 us, k_hess_second 584.
 // At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
 // plus accumulation registers and run one wave per SIMD; with the bound they spill a few
 // hundred bytes per lane and run 17% faster (the value variants fit without spilling).
@@ -1212,16 +1213,22 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item
             }
             T* out = reinterpret_cast<T*>(partials) + (size_t)ii * NACC;
             constexpr int NOUT = !DERIV ? A_VAL + 1 : KK == KK_PIXEL ? A_K4 + 1 : NACC;   // the sums this pass forms
+            if constexpr (std::is_same<T, double>::value) {
+                constexpr int NV = NOUT + (KK != KK_NONE ? NKK_USED : 0);
+                double v[NV];
 #pragma unroll
-            for (int f = 0; f < NOUT; ++f) {
-                const T s = wave_sum(acc[f]);
-                if (lane == 0) out[f] = s;
-            }
-            if constexpr (KK != KK_NONE) {
+                for (int f = 0; f < NV; ++f) v[f] = f < NOUT ? acc[f] : kh[f - NOUT];
+                int f;
+                const double s = wave_sums_dealt<NV>(v, lane, f);
+                if (f >= 0) {
+                    if (f < NOUT) out[f] = s;
+                    else a.kk[(size_t)ii * NKK + f - NOUT] = s;
+                }
+            } else {
 #pragma unroll
-                for (int f = 0; f < NKK_USED; ++f) {
-                    const double s = wave_sum(kh[f]);
-                    if (lane == 0) a.kk[(size_t)ii * NKK + f] = s;
+                for (int f = 0; f < NOUT; ++f) {
+                    const T s = wave_sum(acc[f]);
+                    if (lane == 0) out[f] = s;
                 }
             }
         }
@@ -1521,34 +1528,46 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
             }
             hess_second_strip<L>(my, (double)c, (double)r0, Gs, Gg, H, acc, t2, live);
         }
+        double v[NHG_GEO + NACC - A_UX];
 #pragma unroll
-        for (int f = 0; f < NHG_GEO; ++f) {
-            const double v = wave_sum(H[f]);
-            if (lane == 0) out[f] = v;
+        for (int f = 0; f < NHG_GEO; ++f) v[f] = H[f];
+#pragma unroll
+        for (int f = 0; f < NACC - A_UX; ++f) v[NHG_GEO + f] = acc[f];
+        int f;
+        const double sum = wave_sums_dealt<NHG_GEO + NACC - A_UX>(v, lane, f);
+        if (f >= 0) {
+            if (f < NHG_GEO) out[f] = sum;
+            else a.partials[(size_t)ii * NACC + A_UX + f - NHG_GEO] = sum;
         }
         if (lane >= NHG_GEO && lane < NHG) out[lane] = 0.0;
-#pragma unroll
-        for (int f = 0; f < NACC - A_UX; ++f) {
-            const double v = wave_sum(acc[f]);
-            if (lane == 0) a.partials[(size_t)ii * NACC + A_UX + f] = v;
-        }
         j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
     }
 }
 
 // One wave per work item.  The item's pixels (stored backgrounds and own profile values of
-// the listed boxes) are cut into runs of HPX rows of one strip; the runs, taken by row
-// index and then by strip, are dealt round-robin to the lanes, so that an item of fewer
-// than 64 strips still fills the wave.  The wave adds its NHG sums onto hg[item], which
+// the listed boxes) are cut into runs of R rows of one strip; the runs, taken by row index and
+// then by strip, are dealt round-robin to the wave's 32 pairs of lanes, so that an item of
+// fewer than 64 strips still fills the wave.  The wave adds its NHG sums onto hg[item], which
 // k_hess_second has filled with the second-derivative terms; the items of sources outside
-// a.active (when given) get zeros.  Launched with two rows and two waves per SIMD: on 1024
-// sources 24% faster per Newton iteration than one row (before the second-derivative terms
-// moved to k_hess_second), and faster than three rows (more spills) or four rows at one
-// wave.
-#ifndef CELESTE_HESS_RUN
-#define CELESTE_HESS_RUN 4
-#endif
-constexpr int HESS_RUN = CELESTE_HESS_RUN;   // rows per run of k_hess_geom
+// a.active (when given) get zeros.
+// Each component costs its two exponentials once per run, so long runs pay, and a lane holds
+// six sums per row beside the 40 of the Hessian: four rows a lane is what fits two waves a
+// SIMD.  So a pair of lanes shares a run of twice as many rows: each takes every other
+// component for all R rows, the even lane downwards and the odd lane upwards, then they
+// exchange the farther halves of their rows' sums and each forms the products of its nearer
+// R / 2.  Runs of four rows on one lane took 748 us on 1024 sources (1.6e7 visits), this 670.
+// A run may start up to R - 1 rows outside its box, where a narrow component must not have
+// underflowed: eight rows with smooth PSFs (the exponent falls by less than 40 in seven rows
+// at the centre), four otherwise (by 450 at the narrowest PSF there may be, sigma = 0.1 px).
+constexpr int HESS_RUN = 8, HESS_RUN_SHARP = 4;   // rows per run of k_hess_geom
+
+// v of the other lane of the pair (lanes 2 i, 2 i + 1).
+__device__ __forceinline__ double pair_swap(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
 
 template <int L, int R>
 __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __restrict__ items,
@@ -1591,55 +1610,46 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
         for (int f = 0; f < NHG; ++f) H[f] = 0.0;
         // runs of R rows per strip: those of the item's first strip, the longest
         const int nk = (min(L, p.h - (it.start / p.w) * L) + R - 1) / R;
-        for (int g = lane; g < it.count * nk; g += 64) {
+        constexpr int HR = R / 2;
+        const bool up = lane & 1;               // this lane walks its run upwards
+        const double sg_row = up ? -1.0 : 1.0;
+        for (int g = lane >> 1; g < it.count * nk; g += 32) {
             const int kr = g / it.count, q = g - kr * it.count;
             int c, r0, nrow;
             strip_geometry(p, it.start + q, L, c, r0, nrow);
             const int kk = kr * R;
-            if (kk >= nrow) continue;
-            const double px = (double)c, py0 = (double)(r0 + kk);
-            // first derivatives of the star and galaxy profiles down the run, summed over the
-            // components: each component's value by the strip recurrence, z affine in the row
-            double S[R][2], F[R][6];
+            if (kk >= nrow) continue;   // both lanes of the pair
+            const double px = (double)c, py0 = (double)(r0 + kk + (up ? R - 1 : 0));
+            // first derivatives of the galaxy profile along the run (row i of the lane is row
+            // kk + i of the strip, or kk + R - 1 - i upwards), summed over every other live
+            // component: each component's value by the strip recurrence, z affine in the row
+            double F[R][6];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                S[r][0] = S[r][1] = 0.0;
+            for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int f = 0; f < 6; ++f) F[r][f] = 0.0;
-            }
 #pragma unroll 1
             for (int grp = 0; grp < NPSF; ++grp) {
-                const bool star = (live >> grp) & 1;
-                if (!star && !((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
+                if (!((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
                 const double* es = my + grp;
                 const double dx = px - es[H_CX * NCP], dy = py0 - es[H_CY * NCP];
                 const double h2x = -0.5 * (dx * dx), mxy = -(dx * dy), h2y = -0.5 * (dy * dy);
-                const double mdx = -dx, mdyh = -(dy + 0.5);
-                if (star) {
-                    const double a = es[H_A * NCP], b = es[H_B * NCP], d = es[H_D * NCP];
-                    double n = fexp(fma(a, h2x, fma(b, mxy, fma(d, h2y, es[H_LW * NCP]))), t2);
-                    double rt = fexp(clamp_arg(fma(b, mdx, d * mdyh)), t2);
-                    const double rdy = es[H_RDY * NCP];
-                    const double zx0 = fma(a, dx, b * dy), zy0 = fma(b, dx, d * dy);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const double zx = fma(b, (double)r, zx0), zy = fma(d, (double)r, zy0);
-                        S[r][0] = fma(n, zx, S[r][0]);
-                        S[r][1] = fma(n, zy, S[r][1]);
-                        if (r + 1 < R) {
-                            n = n * rt;
-                            rt = rt * rdy;
-                        }
-                    }
-                }
-                auto gal = [&](const double* __restrict__ e, double n, double rt) {
+                const double mdx = -sg_row * dx, mdyh = -fma(sg_row, dy, 0.5);
+                for_live_pairs(live, grp, [&](int s0, int s1) {
+                    const double* e = my + (up ? s1 : s0);
                     const double a = e[H_A * NCP], b = e[H_B * NCP], d = e[H_D * NCP];
+                    const double xs2[2] = {fma(a, h2x, fma(b, mxy, fma(d, h2y, e[H_LW * NCP]))),
+                                           clamp_arg(fma(b, mdx, d * mdyh))};
+                    double ex[2];
+                    fexps<2>(xs2, ex, t2);
+                    double n = ex[0], rt = ex[1];
                     const double rdy = e[H_RDY * NCP];
                     const double wt = e[H_WT * NCP], sg = e[H_SGN * NCP], wnu = e[H_WNU * NCP];
                     const double zx0 = fma(a, dx, b * dy), zy0 = fma(b, dx, d * dy);
+                    const double bs = b * sg_row, ds = d * sg_row;
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        const double zx = fma(b, (double)r, zx0), zy = fma(d, (double)r, zy0);
+                        const double zx = fma(bs, (double)r, zx0), zy = fma(ds, (double)r, zy0);
                         const double wn = wt * n, vn = wnu * n;
                         F[r][0] = fma(wn, zx, F[r][0]);
                         F[r][1] = fma(wn, zy, F[r][1]);
@@ -1652,22 +1662,50 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
                             rt = rt * rdy;
                         }
                     }
-                };
-                for_live_pairs(live, grp, [&](int s0, int s1) {
-                    double n[2], rt[2];
-                    seed_pair(my + s0, my + s1, h2x, mxy, h2y, mdx, mdyh, n, rt, t2);
-                    gal(my + s0, n[0], rt[0]);
-                    gal(my + s1, n[1], rt[1]);
                 });
+            }
+            // the lane's nearer rows, with the other lane's share of them
+#pragma unroll
+            for (int r = 0; r < HR; ++r)
+#pragma unroll
+                for (int f = 0; f < 6; ++f) F[r][f] += pair_swap(F[R - 1 - r][f]);
+            // the star profile's, for those rows
+            double S[HR][2];
+#pragma unroll
+            for (int r = 0; r < HR; ++r) S[r][0] = S[r][1] = 0.0;
+#pragma unroll 1
+            for (int grp = 0; grp < NPSF; ++grp) {
+                if (!((live >> grp) & 1)) continue;
+                const double* es = my + grp;
+                const double dx = px - es[H_CX * NCP], dy = py0 - es[H_CY * NCP];
+                const double a = es[H_A * NCP], b = es[H_B * NCP], d = es[H_D * NCP];
+                const double zx0 = fma(a, dx, b * dy), zy0 = fma(b, dx, d * dy);
+                const double xs2[2] = {fma(-0.5, fma(dx, zx0, dy * zy0), es[H_LW * NCP]),
+                                       clamp_arg(-fma(sg_row, zy0, 0.5 * d))};
+                double ex[2];
+                fexps<2>(xs2, ex, t2);
+                double n = ex[0], rt = ex[1];
+                const double rdy = es[H_RDY * NCP];
+                const double bs = b * sg_row, ds = d * sg_row;
+#pragma unroll
+                for (int r = 0; r < HR; ++r) {
+                    S[r][0] = fma(n, fma(bs, (double)r, zx0), S[r][0]);
+                    S[r][1] = fma(n, fma(ds, (double)r, zy0), S[r][1]);
+                    if (r + 1 < HR) {
+                        n = n * rt;
+                        rt = rt * rdy;
+                    }
+                }
             }
             // products of first derivatives and the k-block entries, row by row (the pixel
             // scalars from the row's stored background and own values)
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int row = kk + r < nrow ? kk + r : kk;   // rows past the strip reuse row kk
+            for (int r = 0; r < HR; ++r) {
+                const int at = up ? kk + R - 1 - r : kk + r;
+                const int row = at < nrow ? at : kk;   // rows past the strip reuse row kk
                 const size_t gi = (size_t)im.pix_offset + (size_t)(r0 + row) * im.W + c;
                 const double x = xs[gi];
-                if (!(kk + r < nrow && x == x)) continue;
+                if (!(at < nrow && x == x)) continue;
                 const size_t vi = (size_t)p.visit_off + (size_t)(r0 + row - p.r0) * p.w + (c - p.c0);
                 const double fs = own[2 * vi], fg = own[2 * vi + 1];
                 const double Es = k[C_K1] * fs + k[C_K2] * fg;
@@ -1681,42 +1719,46 @@ __global__ void __launch_bounds__(256, 2) k_hess_geom(AdjArgs a, const Item* __r
                 const double lEE = -x * inv2 * (1.0 + 3.0 * rr);
                 const double lEV = x * inv2 * inv;
                 const double A = lE - 2.0 * Es * lV;
-                double Eg[6], Vg[6];
+                // E_g = k1 S_g + k2 F_g and V_g = vS S_g + vF F_g (S_g = 0 but for the position),
+                // so every entry is a combination of products of S and F with the scalars below
+                const double k1 = k[C_K1], k2 = k[C_K2];
+                const double vS = 2.0 * (k[C_K3] * fs - Es * k1), vF = 2.0 * (k[C_K4] * fg - Es * k2);
+                const double lV2 = 2.0 * lV, lEE2 = lEE - lV2;
+                const double cSS = fma(k1, fma(lEE2, k1, 2.0 * (lEV * vS)), lV2 * k[C_K3]);
+                const double cFF = fma(k2, fma(lEE2, k2, 2.0 * (lEV * vF)), lV2 * k[C_K4]);
+                const double cSF = fma(lEE2 * k1, k2, lEV * fma(k1, vF, k2 * vS));
+                const double S0 = S[r][0], S1 = S[r][1];
+                const double Q0 = fma(cSS, S0, cSF * F[r][0]), Q1 = fma(cSS, S1, cSF * F[r][1]);
+                const double R0 = fma(cSF, S0, cFF * F[r][0]), R1 = fma(cSF, S1, cFF * F[r][1]);
+                H[HG_XX] = fma(Q0, S0, fma(R0, F[r][0], H[HG_XX]));
+                H[HG_XY] = fma(Q0, S1, fma(R0, F[r][1], H[HG_XY]));
+                H[HG_YY] = fma(Q1, S1, fma(R1, F[r][1], H[HG_YY]));
 #pragma unroll
-                for (int gg = 0; gg < 6; ++gg) {
-                    const double Sg = gg < 2 ? S[r][gg] : 0.0;
-                    Eg[gg] = k[C_K1] * Sg + k[C_K2] * F[r][gg];
-                    Vg[gg] = 2.0 * (k[C_K3] * fs) * Sg + 2.0 * (k[C_K4] * fg) * F[r][gg] - 2.0 * Es * Eg[gg];
-                }
-                const double lEE2 = lEE - 2.0 * lV, lV2 = 2.0 * lV;
-#pragma unroll
-                for (int qq = 0; qq < NHG_GEO; ++qq) {
+                for (int qq = HG_YY + 1; qq < NHG_GEO; ++qq) {
                     const int g1 = hg_row(qq), h1 = hg_col(qq);
-                    double v = (lEE2 * Eg[g1] + lEV * Vg[g1]) * Eg[h1] + (lEV * Eg[g1]) * Vg[h1] +
-                               lV2 * k[C_K4] * F[r][g1] * F[r][h1];
-                    if (g1 < 2 && h1 < 2) v += lV2 * k[C_K3] * S[r][g1] * S[r][h1];
-                    H[qq] += v;
+                    H[qq] = fma(g1 == 0 ? R0 : g1 == 1 ? R1 : cFF * F[r][g1], F[r][h1], H[qq]);
                 }
-                const double Rc = lEE - 2.0 * lEV * Es - 2.0 * lV;
+                const double Rc = fma(-2.0 * lEV, Es, lEE2);
+                const double rS = fma(Rc, k1, lEV * vS), rF = fma(Rc, k2, lEV * vF);
+                const double ls = lEV * (fs * fs), lg = lEV * (fg * fg);
+                const double cF[4] = {fs * rF, fma(fg, rF, A), ls * k2, fma(lg, k2, lV2 * fg)};
+                const double cS[4] = {fma(fs, rS, A), fg * rS, fma(ls, k1, lV2 * fs), lg * k1};
 #pragma unroll
                 for (int qq = 0; qq < 5; ++qq) {
                     const int g1 = qq < 2 ? qq : qq + 1;
-                    const double Sg = g1 < 2 ? S[r][g1] : 0.0;
-                    const double Rv = Rc * Eg[g1] + lEV * Vg[g1];
                     double* o = H + NHG_GEO + 4 * qq;
-                    o[0] += fs * Rv + A * Sg;
-                    o[1] += fg * Rv + A * F[r][g1];
-                    o[2] += lEV * (fs * fs) * Eg[g1] + lV2 * fs * Sg;
-                    o[3] += lEV * (fg * fg) * Eg[g1] + lV2 * fg * F[r][g1];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (g1 < 2) o[i] = fma(cS[i], S[r][g1], o[i]);
+                        o[i] = fma(cF[i], F[r][g1], o[i]);
+                    }
                 }
             }
         }
-        // the item's sums side by side (one sum at a time, each shuffle and lane 0's
-        // read-modify-write would wait in turn); lane f adds sum f onto the
-        // second-derivative terms of k_hess_second
-        wave_sums<NHG>(H);
-        const double hv = lane_pick<NHG>(H, lane);
-        if (lane < NHG) hg[(size_t)ii * NHG + lane] += hv;
+        // added onto the second-derivative terms of k_hess_second
+        int f;
+        const double hv = wave_sums_dealt<NHG>(H, lane, f);
+        if (f >= 0) hg[(size_t)ii * NHG + f] += hv;
         j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
     }
 }
@@ -2224,13 +2266,17 @@ hipError_t launch_hess_geom(const AdjArgs& a, const double* nu, double* hg, int 
             hipError_t e = launch_fill_int(a.counter, 0, 1, st);
             if (e != hipSuccess) return e;
         }
+#define CEL_GEOM(LL, RR)                                                                                           \
+    hipLaunchKernelGGL((k_hess_geom<LL, RR>), dim3(grid), dim3(64 * wpb), lds, st, a, g.items, g.pairs, g.images,  \
+                       g.x, a.bg, a.tab, a.coef, a.fg, nu, hg)
 #define CEL_HG(LL)                                                                                                 \
     if (pass == 0)                                                                                                 \
         hipLaunchKernelGGL((k_hess_second<LL>), dim3(grid), dim3(64 * wpb), lds, st, a, g.items, g.pairs, g.images, \
                            g.x, a.bg, a.tab, a.coef, a.fg, nu, hg);                                                \
+    else if (g.smooth)                                                                                             \
+        CEL_GEOM(LL, (HESS_RUN < LL ? HESS_RUN : LL));                                                             \
     else                                                                                                           \
-        hipLaunchKernelGGL((k_hess_geom<LL, (HESS_RUN < LL ? HESS_RUN : LL)>), dim3(grid), dim3(64 * wpb), lds, st,    \
-                           a, g.items, g.pairs, g.images, g.x, a.bg, a.tab, a.coef, a.fg, nu, hg)
+        CEL_GEOM(LL, HESS_RUN_SHARP)
         if (L == 16)
             CEL_HG(16);
         else if (L == 8)
@@ -2238,6 +2284,7 @@ hipError_t launch_hess_geom(const AdjArgs& a, const double* nu, double* hg, int 
         else
             CEL_HG(4);
 #undef CEL_HG
+#undef CEL_GEOM
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
