@@ -149,7 +149,8 @@ typedef struct celeste_plan_info {
     int32_t grid_blocks;   /* grid size (blocks) of the grid-stride strip and adjoint launches */
     int32_t tile_h, tile_w;
     int32_t dynamic_queue; /* 1: items popped from a device counter; 0: static round robin */
-    int32_t strip_rows;    /* pixels per strip: a lane walks one column of a box this many rows */
+    int32_t strip_rows;    /* pixels per strip: a lane walks one column of a box this many rows
+                              (see celeste_plan_set_launch for a new plan's passes) */
     int32_t render_mode;   /* 0: strips per conflict-free class of boxes; 1: binned tiles evaluating
                               the Gaussians; 2 (default): one strip pass storing each visit's own
                               profile values, then a binned-tile gather (the fused adjoint reuses
@@ -340,9 +341,11 @@ int celeste_sweep(celeste_plan* plan, double* theta_inout, const int32_t* batch_
  * unit), dynamic_queue (0/1), render tile tile_h x tile_w (tile_w divides 64; tile_h * tile_w = 64, 128 or 256),
  * strip_rows (4, 8 or 16 pixels per strip) and render_mode (see celeste_plan_info).  A new
  * plan starts at chunk 64, 4 waves per block, grid 0, static queue, 16 x 16 tiles, 16-row
- * strips, render mode 2.  Rebuilds work items and render tiles (synchronous).  If grown
- * tile buffers cannot be allocated it returns CELESTE_ENOMEM and the plan keeps its
- * previous configuration. */
+ * strips, render mode 2; until this is called, the passes of a plan too small to fill the
+ * device with 16-row strips take lower ones (the plan's items, and info, stay the 16-row
+ * ones).  Afterwards every pass takes strip_rows.  Rebuilds work items and render tiles
+ * (synchronous).  If grown tile buffers cannot be allocated it returns CELESTE_ENOMEM and
+ * the plan keeps its previous configuration. */
 int celeste_plan_set_launch(celeste_plan* plan, int chunk, int waves_per_block, int grid_blocks,
                             int dynamic_queue, int tile_h, int tile_w, int strip_rows, int render_mode);
 

@@ -51,6 +51,15 @@ bool finite(double v) { return std::isfinite(v); }
 
 }  // namespace
 
+// The boxes cut into strips of `rows` rows, and those into work items.
+struct Cut {
+    int rows = 16;
+    std::vector<Item> items;
+    std::vector<int32_t> ptr;    // [n_pairs + 1] first item of each box
+    Item* d_items = nullptr;
+    PairDev* d_pairs = nullptr;  // the boxes with their items
+};
+
 struct celeste_plan {
     int device = 0;
     int n_img = 0, n_src = 0;
@@ -58,7 +67,6 @@ struct celeste_plan {
     std::vector<celeste_image> images;
     std::vector<int32_t> patch_ptr;
     std::vector<PairDev> pairs;
-    std::vector<Item> items;
     std::vector<int32_t> nbr;
     std::vector<TileDev> tiles;
     std::vector<int32_t> tile_list;
@@ -68,17 +76,18 @@ struct celeste_plan {
     int n_cu = 256;
 
     // launch configuration
-    int chunk = 64, wpb = 4, grid = 0, dynamic = 0, tile_h = 16, tile_w = 16, rows = 16;
+    int chunk = 64, wpb = 4, grid = 0, dynamic = 0, tile_h = 16, tile_w = 16;
     // 0: strips per conflict-free class, 1: binned tiles, 2: stored values + tile gather,
     // 3: stored values, background gathered inside the fused adjoint (no planes)
     int render_mode = 2;
     bool use_graph = false;
+    // cuts[0] is the launch configuration's; until celeste_plan_set_launch is called the passes
+    // of a smaller plan take cuts of lower strips (choose_cuts).  cut: the one in use.
+    Cut cuts[3];
+    Cut *cut = &cuts[0], *cut_eval = &cuts[0], *cut_newton = &cuts[0];
 
     // device memory
     celeste_image* d_images = nullptr;
-    PairDev* d_pairs = nullptr;
-    Item* d_items = nullptr;
-    size_t cap_items = 0;
     int32_t* d_nbr = nullptr;
     TileDev* d_tiles = nullptr;
     size_t cap_tiles = 0;
@@ -90,8 +99,8 @@ struct celeste_plan {
     double* d_tab2 = nullptr;    // dual tables
     double* d_coef2 = nullptr;
     double* d_partials = nullptr;
-    double* d_kk = nullptr;          // [cap_items][NKK] brightness-factor Hessian blocks
-    double* d_hg = nullptr;          // [cap_items][NHG] closed-form position / shape Hessian blocks
+    double* d_kk = nullptr;          // [max_items][NKK] brightness-factor Hessian blocks
+    double* d_hg = nullptr;          // [max_items][NHG] closed-form position / shape Hessian blocks
     double* d_nu = nullptr;          // [NGAL] nu of each galaxy component (closed-form pass)
     int hess_mode = 0;               // 0: closed-form block pass, 1: tangent passes of the adjoint
     double* d_E = nullptr;
@@ -119,7 +128,7 @@ struct celeste_plan {
     uint8_t* d_done = nullptr;
     int32_t* d_list_src = nullptr;   // [n_src]
     int32_t* d_list_pair = nullptr;  // [n_pairs]
-    int32_t* d_list_item = nullptr;  // [cap_items]
+    int32_t* d_list_item = nullptr;  // [max_items]
     int32_t* d_list_npair = nullptr; // [n_pairs] boxes whose stored values a Newton call renders
     int32_t* d_list_nitem = nullptr; // [max_items] their items
     size_t cap_list_item = 0, cap_list_src = 0, cap_list_pair = 0;
@@ -159,8 +168,8 @@ struct celeste_plan {
     Geometry geom() const {
         Geometry g;
         g.images = d_images;
-        g.pairs = d_pairs;
-        g.items = d_items;
+        g.pairs = cut->d_pairs;
+        g.items = cut->d_items;
         g.nbr = d_nbr;
         g.x = d_x;
         g.consts = consts;
@@ -179,23 +188,70 @@ namespace {
 // column of a box), in box order.
 int64_t strips_of(const PairDev& pd, int rows) { return (int64_t)pd.w * ((pd.h + rows - 1) / rows); }
 
-void build_items(celeste_plan* p) {
-    p->items.clear();
+int64_t count_items(const celeste_plan* p, int rows, int chunk) {
+    int64_t n = 0;
+    for (const PairDev& pd : p->pairs) n += (strips_of(pd, rows) + chunk - 1) / chunk;
+    return n;
+}
+
+void build_items(const celeste_plan* p, Cut& c) {
+    c.items.clear();
+    c.ptr.assign(1, 0);
     for (size_t i = 0; i < p->pairs.size(); ++i) {
-        PairDev& pd = p->pairs[i];
-        const int n = (int)strips_of(pd, p->rows);
-        pd.item_begin = (int32_t)p->items.size();
+        const int n = (int)strips_of(p->pairs[i], c.rows);
         for (int s = 0; s < n; s += p->chunk) {
             Item it;
             it.pair = (int32_t)i;
             it.start = s;
             it.count = std::min(p->chunk, n - s);
             it.pad = 0;
-            p->items.push_back(it);
+            c.items.push_back(it);
         }
-        pd.item_end = (int32_t)p->items.size();
+        c.ptr.push_back((int32_t)c.items.size());
     }
 }
+
+// Strip heights of a new plan.  A lane walks its strip alone, so a low strip shortens every
+// pass, and a high one spares instructions (each strip seeds its Gaussians again, and a
+// wave's items overlap fewer of them).  Lower strips win as long as no SIMD gets a second
+// wave: us a call at 16 / 8 / 4 rows,
+//   gradient, 8 sources (275 items of 4 rows)       66 / 59 / 56
+//   gradient, 20 sources (565 items of 8 rows)      69 / 63 / 71
+//   gradient, 50 sources (850 of 16, 1510 of 8)     77 / 79 / 86
+//   gradient, 500 sources                          295 / 314 / 413
+// The Newton and Hessian passes do more for each item and run over lists of the plan's
+// sources, where fewer, longer items leave SIMDs idle sooner: lower strips pay up to some
+// 16 items a SIMD for the whole plan,
+//   3 steps, 50 of 500 sources (9440 items of 16)  953 / 810 / 969
+//   3 steps, all of 500 sources                   2990 / 3001 / 3746
+//   2 steps, 1024 sources (19945 of 16)           5694 / 5847 / 7466
+// The plan decides, not the call's list, so a source's steps stay the same in every list.
+void choose_cuts(celeste_plan* p) {
+    const int64_t full = 4 * (int64_t)p->n_cu;   // one wave per SIMD
+    int eval = 16, newton = count_items(p, 16, p->chunk) <= 16 * full ? 8 : 16;
+    if (count_items(p, 4, p->chunk) <= full)
+        eval = newton = 4;
+    else if (count_items(p, 8, p->chunk) <= full)
+        eval = 8;
+    int n = 1;
+    auto cut_of = [&](int rows) {
+        for (int i = 0; i < n; ++i)
+            if (p->cuts[i].rows == rows) return &p->cuts[i];
+        p->cuts[n].rows = rows;
+        build_items(p, p->cuts[n]);
+        return &p->cuts[n++];
+    };
+    p->cut_eval = cut_of(eval);
+    p->cut_newton = cut_of(newton);
+}
+
+// The cut that a call's passes take, until the end of the scope.
+struct UseCut {
+    celeste_plan* p;
+    Cut* was;
+    UseCut(celeste_plan* plan, Cut* c) : p(plan), was(plan->cut) { p->cut = c; }
+    ~UseCut() { p->cut = was; }
+};
 
 // Greedy colouring of the box-overlap graph (largest boxes first): boxes of one class
 // never share a pixel, so a class can add its light to the planes without atomics.
@@ -225,15 +281,17 @@ void build_pair_classes(celeste_plan* p) {
     }
 }
 
+// (of cuts[0]: the mode that takes classes is set with the launch, and so is every pass's cut)
 void build_class_items(celeste_plan* p) {
+    const Cut& c = p->cuts[0];
     p->cls_ptr.assign(p->n_class + 1, 0);
     for (size_t i = 0; i < p->pairs.size(); ++i)
-        p->cls_ptr[p->pair_class[i] + 1] += p->pairs[i].item_end - p->pairs[i].item_begin;
-    for (int c = 0; c < p->n_class; ++c) p->cls_ptr[c + 1] += p->cls_ptr[c];
-    p->cls_items.assign(p->items.size(), 0);
+        p->cls_ptr[p->pair_class[i] + 1] += c.ptr[i + 1] - c.ptr[i];
+    for (int k = 0; k < p->n_class; ++k) p->cls_ptr[k + 1] += p->cls_ptr[k];
+    p->cls_items.assign(c.items.size(), 0);
     std::vector<int32_t> fill(p->cls_ptr.begin(), p->cls_ptr.end() - 1);
     for (size_t i = 0; i < p->pairs.size(); ++i)
-        for (int it = p->pairs[i].item_begin; it < p->pairs[i].item_end; ++it)
+        for (int it = c.ptr[i]; it < c.ptr[i + 1]; ++it)
             p->cls_items[fill[p->pair_class[i]]++] = it;
 }
 
@@ -321,8 +379,16 @@ void build_nbr(celeste_plan* p) {
 }
 
 int upload_geometry(celeste_plan* p) {
-    HIPCHK(hipMemcpy(p->d_pairs, p->pairs.data(), p->pairs.size() * sizeof(PairDev), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(p->d_items, p->items.data(), p->items.size() * sizeof(Item), hipMemcpyHostToDevice));
+    std::vector<PairDev> pairs(p->pairs);
+    for (const Cut& c : p->cuts) {
+        if (c.ptr.empty()) continue;   // not in use
+        for (size_t i = 0; i < pairs.size(); ++i) {
+            pairs[i].item_begin = c.ptr[i];
+            pairs[i].item_end = c.ptr[i + 1];
+        }
+        HIPCHK(hipMemcpy(c.d_pairs, pairs.data(), pairs.size() * sizeof(PairDev), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(c.d_items, c.items.data(), c.items.size() * sizeof(Item), hipMemcpyHostToDevice));
+    }
     if (!p->cls_items.empty())
         HIPCHK(hipMemcpy(p->d_cls_items, p->cls_items.data(), p->cls_items.size() * sizeof(int32_t),
                          hipMemcpyHostToDevice));
@@ -487,7 +553,7 @@ Scope scope_all(const celeste_plan* p) {
     Scope s;
     s.src = Sel{nullptr, 0, p->n_src};
     s.pair = Sel{nullptr, 0, (int32_t)p->pairs.size()};
-    s.item = Sel{nullptr, 0, (int32_t)p->items.size()};
+    s.item = Sel{nullptr, 0, (int32_t)p->cut->items.size()};
     return s;
 }
 
@@ -496,8 +562,7 @@ Scope scope_source(const celeste_plan* p, int s) {
     const int pb = p->patch_ptr[s], pe = p->patch_ptr[s + 1];
     sc.src = Sel{nullptr, s, 1};
     sc.pair = Sel{nullptr, pb, pe - pb};
-    const int ib = pb < pe ? p->pairs[pb].item_begin : 0;
-    const int ie = pb < pe ? p->pairs[pe - 1].item_end : 0;
+    const int ib = p->cut->ptr[pb], ie = p->cut->ptr[pe];
     sc.item = Sel{nullptr, ib, ie - ib};
     return sc;
 }
@@ -564,8 +629,8 @@ int render(celeste_plan* p, hipStream_t st, bool sums = false) {
     p->fg_valid = false;
     if (p->render_mode == 1 || (sums && p->render_mode == 0)) return render_tiles(p, sums, st);
     if (p->render_mode == 2 || p->render_mode == 3) {
-        const Sel all{nullptr, 0, (int32_t)p->items.size()};
-        HIPCHK(launch_strip_fg(all, p->geom(), p->d_tab1, p->d_fg, p->rows, p->launch_grid(), p->wpb,
+        const Sel all{nullptr, 0, (int32_t)p->cut->items.size()};
+        HIPCHK(launch_strip_fg(all, p->geom(), p->d_tab1, p->d_fg, p->cut->rows, p->launch_grid(), p->wpb,
                                p->d_status, st));
         p->fg_valid = true;
         // mode 3: no planes (the adjoint gathers from stored values) unless sums are asked for
@@ -576,7 +641,7 @@ int render(celeste_plan* p, hipStream_t st, bool sums = false) {
     const Geometry g = p->geom();
     for (int c = 0; c < p->n_class; ++c) {
         const Sel sel{p->d_cls_items + p->cls_ptr[c], 0, p->cls_ptr[c + 1] - p->cls_ptr[c]};
-        HIPCHK(launch_render_strips(sel, g, p->d_tab1, p->d_coef1, p->d_E, p->d_V, p->rows, p->launch_grid(),
+        HIPCHK(launch_render_strips(sel, g, p->d_tab1, p->d_coef1, p->d_E, p->d_V, p->cut->rows, p->launch_grid(),
                                     p->wpb, p->d_status, st));
     }
     return CELESTE_OK;
@@ -613,7 +678,7 @@ int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tange
     }
     a.status = p->d_status;
     const int grid = grid_override > 0 ? grid_override : p->launch_grid();
-    HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, p->wpb, p->rows, st));
+    HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, p->wpb, p->cut->rows, st));
     return CELESTE_OK;
 }
 
@@ -655,7 +720,7 @@ int background(celeste_plan* p, const Sel& items, hipStream_t st, bool stored = 
     a.fg = stored ? p->d_fg : nullptr;
     a.bg = p->d_bg;
     a.status = p->d_status;
-    HIPCHK(launch_background(a, p->launch_grid(), p->wpb, p->rows, st));
+    HIPCHK(launch_background(a, p->launch_grid(), p->wpb, p->cut->rows, st));
     return CELESTE_OK;
 }
 
@@ -725,8 +790,18 @@ int plain_sequence(celeste_plan* p, const double* theta, const uint8_t* active, 
     return CELESTE_OK;
 }
 
+int total_sequence(celeste_plan* p, const double* theta, double* out, hipStream_t st) {
+    const Scope sc = scope_all(p);
+    CHK(validate_theta(p, theta, nullptr, nullptr, p->n_src, st));
+    CHK(prep(p, theta, sc.pair, false, DIR_NONE, nullptr, 0, st));
+    CHK(render(p, st, true));
+    HIPCHK(launch_tile_total(p->d_tile_sums, (int)p->tiles.size(), theta, p->consts, p->n_src, p->d_tt_part, out,
+                             p->d_status, st));
+    return CELESTE_OK;
+}
+
 int config_code(const celeste_plan* p) {
-    return ((((p->chunk * 8 + p->wpb) * 2 + p->dynamic) * 32 + p->rows) * 2 + p->render_mode) * 1000003 +
+    return ((((p->chunk * 8 + p->wpb) * 2 + p->dynamic) * 32 + p->cut->rows) * 2 + p->render_mode) * 1000003 +
            p->launch_grid() * 131 + p->tile_h * 7 + p->tile_w;
 }
 
@@ -743,7 +818,7 @@ void scope_lists(const celeste_plan* p, const int32_t* src, int n, HostScope& hs
         hs.src.push_back(s);
         for (int pi = p->patch_ptr[s]; pi < p->patch_ptr[s + 1]; ++pi) {
             hs.pair.push_back(pi);
-            for (int it = p->pairs[pi].item_begin; it < p->pairs[pi].item_end; ++it) hs.item.push_back(it);
+            for (int it = p->cut->ptr[pi]; it < p->cut->ptr[pi + 1]; ++it) hs.item.push_back(it);
         }
     }
     // items of more strips first, so that a launch over the list ends on short items and its
@@ -753,12 +828,12 @@ void scope_lists(const celeste_plan* p, const int32_t* src, int n, HostScope& hs
     const size_t n_it = hs.item.size() - i0;
     if (n_it < 2) return;
     int mx = 0;
-    for (size_t i = i0; i < hs.item.size(); ++i) mx = std::max(mx, (int)p->items[hs.item[i]].count);
+    for (size_t i = i0; i < hs.item.size(); ++i) mx = std::max(mx, (int)p->cut->items[hs.item[i]].count);
     std::vector<size_t> pos(mx + 2, 0);
-    for (size_t i = i0; i < hs.item.size(); ++i) pos[mx - p->items[hs.item[i]].count + 1]++;
+    for (size_t i = i0; i < hs.item.size(); ++i) pos[mx - p->cut->items[hs.item[i]].count + 1]++;
     for (int k = 1; k <= mx + 1; ++k) pos[k] += pos[k - 1];
     std::vector<int32_t> out(n_it);
-    for (size_t i = i0; i < hs.item.size(); ++i) out[pos[mx - p->items[hs.item[i]].count]++] = hs.item[i];
+    for (size_t i = i0; i < hs.item.size(); ++i) out[pos[mx - p->cut->items[hs.item[i]].count]++] = hs.item[i];
     std::copy(out.begin(), out.end(), hs.item.begin() + i0);
 }
 
@@ -822,7 +897,7 @@ void neighbour_lists(const celeste_plan* p, const HostScope& hs, std::vector<int
     for (size_t q = 0; q < mark.size(); ++q)
         if (mark[q]) {
             npair.push_back((int32_t)q);
-            for (int it = p->pairs[q].item_begin; it < p->pairs[q].item_end; ++it) nitem.push_back(it);
+            for (int it = p->cut->ptr[q]; it < p->cut->ptr[q + 1]; ++it) nitem.push_back(it);
         }
 }
 
@@ -833,7 +908,7 @@ void neighbour_lists(const celeste_plan* p, const HostScope& hs, std::vector<int
 int upload_scope(celeste_plan* p, const HostScope& hs, bool stored, Scope* render, hipStream_t st) {
     std::vector<int32_t> npair, nitem;
     if (stored) neighbour_lists(p, hs, npair, nitem);
-    const bool restrict_render = stored && 2 * nitem.size() < p->items.size();
+    const bool restrict_render = stored && 2 * nitem.size() < p->cut->items.size();
     if (restrict_render)
         CHK(upload(p, {{&hs.src, p->d_list_src}, {&hs.pair, p->d_list_pair}, {&hs.item, p->d_list_item},
                        {&npair, p->d_list_npair}, {&nitem, p->d_list_nitem}},
@@ -852,7 +927,7 @@ int upload_scope(celeste_plan* p, const HostScope& hs, bool stored, Scope* rende
 // holds a full render's values).
 int render_stored(celeste_plan* p, const double* theta, const Scope& render, hipStream_t st) {
     CHK(prep(p, theta, render.pair, false, DIR_NONE, nullptr, 0, st));
-    HIPCHK(launch_strip_fg(render.item, p->geom(), p->d_tab1, p->d_fg, p->rows, p->launch_grid(), p->wpb,
+    HIPCHK(launch_strip_fg(render.item, p->geom(), p->d_tab1, p->d_fg, p->cut->rows, p->launch_grid(), p->wpb,
                            p->d_status, st));
     p->fg_valid = false;
     return CELESTE_OK;
@@ -877,16 +952,16 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.dynamic = p->dynamic;
         a.counter = p->d_counter;
         a.status = p->d_status;
-        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->wpb, p->rows, st));
+        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->wpb, p->cut->rows, st));
     }
-    HIPCHK(launch_pair_block(pair, p->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
+    HIPCHK(launch_pair_block(pair, p->cut->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
                              p->d_hw, active, p->d_status, st));
     if (!closed) {
         for (int i = W_UX; i < NW; ++i) {
             if (i == W_FDEV) continue;
             CHK(prep(p, theta, pair, true, DIR_W, nullptr, i, st));
             CHK(adjoint(p, item, nullptr, true, base, true, st));
-            HIPCHK(launch_pair_block(pair, p->d_pairs, p->d_partials, nullptr, nullptr, true, i, p->d_gw, p->d_hw,
+            HIPCHK(launch_pair_block(pair, p->cut->d_pairs, p->d_partials, nullptr, nullptr, true, i, p->d_gw, p->d_hw,
                                      active, p->d_status, st));
         }
     }
@@ -960,6 +1035,7 @@ int batched_elbo_grad_scratch(celeste_plan* p, const double* theta, const uint8_
                               double* grad, double* partials, int* counter, hipStream_t st) {
     // the plan's own partials and counter are set aside for this call only (calls on one
     // plan never overlap)
+    const UseCut use(p, p->cut_eval);
     double* const own_partials = p->d_partials;
     int* const own_counter = p->d_counter;
     p->d_partials = partials;
@@ -970,7 +1046,7 @@ int batched_elbo_grad_scratch(celeste_plan* p, const double* theta, const uint8_
     return rc;
 }
 
-int64_t plan_item_count(const celeste_plan* p) { return (int64_t)p->items.size(); }
+int64_t plan_item_count(const celeste_plan* p) { return (int64_t)p->cuts[0].items.size(); }
 
 int plan_device(const celeste_plan* p) { return p->device; }
 
@@ -1011,7 +1087,7 @@ void celeste_plan_destroy(celeste_plan* p) {
     if (p->h_stage) (void)hipHostFree(p->h_stage);
     if (p->stage_ev) (void)hipEventDestroy(p->stage_ev);
     if (p->sweep_ev) (void)hipEventDestroy(p->sweep_ev);
-    void* bufs[] = {p->d_images, p->d_pairs, p->d_items, p->d_nbr, p->d_tiles, p->d_tile_list, p->d_patch_ptr,
+    void* bufs[] = {p->d_images, p->d_nbr, p->d_tiles, p->d_tile_list, p->d_patch_ptr,
                     p->d_tab1, p->d_coef1, p->d_tab2, p->d_coef2, p->d_partials, p->d_E, p->d_V, p->d_bg,
                     p->d_tile_sums, p->d_status, p->d_counter, p->d_grad, p->d_hess, p->d_theta_trial,
                     p->d_pred, p->d_elbo_cur, p->d_elbo_trial, p->d_radius, p->d_done, p->d_list_src,
@@ -1020,6 +1096,10 @@ void celeste_plan_destroy(celeste_plan* p) {
                     p->d_mix, p->d_scalar, p->d_tt_part, p->d_list_npair, p->d_list_nitem, p->d_wcount};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
+    for (Cut& c : p->cuts) {
+        if (c.d_items) (void)hipFree(c.d_items);
+        if (c.d_pairs) (void)hipFree(c.d_pairs);
+    }
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     for (hipEvent_t& e : p->ev)
         if (e) (void)hipEventDestroy(e);
@@ -1085,7 +1165,8 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
         }
     p->n_visits = voff;
     for (const celeste_image& im : p->images) p->max_pix = std::max<int64_t>(p->max_pix, (int64_t)im.H * im.W);
-    build_items(p);
+    build_items(p, p->cuts[0]);
+    choose_cuts(p);
     build_nbr(p);
     build_pair_classes(p);
     build_class_items(p);
@@ -1098,9 +1179,11 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     int r = CELESTE_OK;
     auto A = [&](int rc) { if (rc != CELESTE_OK && r == CELESTE_OK) r = rc; };
     A(dalloc(&p->d_images, p->n_img, W));
-    A(dalloc(&p->d_pairs, np, W));
-    A(dalloc(&p->d_items, max_items, W));
-    p->cap_items = max_items;
+    for (Cut& c : p->cuts) {
+        if (c.ptr.empty()) continue;
+        A(dalloc(&c.d_pairs, np, W));
+        A(dalloc(&c.d_items, max_items, W));
+    }
     A(dalloc(&p->d_nbr, std::max<size_t>(p->nbr.size(), 1), W));
     A(dalloc(&p->d_tiles, p->tiles.size(), W));
     p->cap_tiles = p->tiles.size();
@@ -1200,7 +1283,7 @@ int celeste_plan_get_info(const celeste_plan* p, celeste_plan_info* info) {
     if (!p || !info) return CELESTE_EINVAL;
     info->n_visits = p->n_visits;
     info->n_pairs = (int64_t)p->pairs.size();
-    info->n_items = (int64_t)p->items.size();
+    info->n_items = (int64_t)p->cuts[0].items.size();
     info->n_tiles = (int64_t)p->tiles.size();
     info->n_nbr = (int64_t)p->nbr.size();
     info->chunk = p->chunk;
@@ -1209,7 +1292,7 @@ int celeste_plan_get_info(const celeste_plan* p, celeste_plan_info* info) {
     info->tile_h = p->tile_h;
     info->tile_w = p->tile_w;
     info->dynamic_queue = p->dynamic;
-    info->strip_rows = p->rows;
+    info->strip_rows = p->cuts[0].rows;
     info->render_mode = p->render_mode;
     info->n_classes = p->n_class;
     info->n_params = p->consts.npar;
@@ -1265,13 +1348,14 @@ int celeste_plan_set_launch(celeste_plan* p, int chunk, int wpb, int grid, int d
             p->cap_tile_list = p->tile_list.size();
         }
     }
-    p->rows = strip_rows;
+    p->cuts[0].rows = strip_rows;
+    p->cut_eval = p->cut_newton = &p->cuts[0];
     p->render_mode = render_mode;
     p->chunk = chunk;
     p->wpb = wpb;
     p->grid = grid;
     p->dynamic = dynamic;
-    build_items(p);
+    build_items(p, p->cuts[0]);
     build_class_items(p);
     return upload_geometry(p);
 }
@@ -1310,6 +1394,7 @@ int celeste_plan_status(celeste_plan* p, hipStream_t st) {
 int celeste_elbo(celeste_plan* p, const double* theta, const uint8_t* active, int mode, double* elbo,
                  hipStream_t st) {
     if (!p || !theta || !elbo || (mode != CELESTE_PLAIN && mode != CELESTE_BATCHED)) return CELESTE_EINVAL;
+    const UseCut use(p, p->cut_eval);
     if (mode == CELESTE_BATCHED) return batched_sequence(p, theta, active, false, elbo, nullptr, st);
     return plain_sequence(p, theta, active, false, elbo, nullptr, st);
 }
@@ -1318,6 +1403,7 @@ int celeste_elbo_grad(celeste_plan* p, const double* theta, const uint8_t* activ
                       double* grad, hipStream_t st) {
     if (!p || !theta || !elbo || !grad || (mode != CELESTE_PLAIN && mode != CELESTE_BATCHED))
         return CELESTE_EINVAL;
+    const UseCut use(p, p->cut_eval);
     if (mode == CELESTE_PLAIN) return plain_sequence(p, theta, active, true, elbo, grad, st);
     if (!p->use_graph) return batched_sequence(p, theta, active, true, elbo, grad, st);
     const void* key[4] = {theta, active, elbo, grad};
@@ -1348,6 +1434,7 @@ int celeste_elbo_grad(celeste_plan* p, const double* theta, const uint8_t* activ
 
 int celeste_hvp(celeste_plan* p, const double* theta, const double* v, double* hv, double* grad, hipStream_t st) {
     if (!p || !theta || !v || !hv) return CELESTE_EINVAL;
+    const UseCut use(p, p->cut_eval);
     const Scope sc = scope_all(p);
     CHK(validate_theta(p, theta, nullptr, nullptr, p->n_src, st));
     CHK(prep(p, theta, sc.pair, false, DIR_NONE, nullptr, 0, st));
@@ -1366,6 +1453,7 @@ int celeste_hessian(celeste_plan* p, const double* theta, const int32_t* src, in
         if (src[j] < 0 || src[j] >= p->n_src || seen[src[j]]) return CELESTE_EINVAL;
         seen[src[j]] = 1;
     }
+    const UseCut use(p, p->cut_newton);
     HostScope hs;
     scope_lists(p, src, n, hs);
     const bool stored = p->render_mode == 2 || p->render_mode == 3;
@@ -1397,7 +1485,7 @@ int celeste_work_counts(celeste_plan* p, const double* theta, int64_t* counts, h
     const Scope sc = scope_all(p);
     CHK(validate_theta(p, theta, nullptr, nullptr, p->n_src, st));
     CHK(prep(p, theta, sc.pair, false, DIR_NONE, nullptr, 0, st));
-    HIPCHK(launch_live_counts(sc.item, p->geom(), p->d_tab1, p->rows, p->d_wcount, p->d_status, st));
+    HIPCHK(launch_live_counts(sc.item, p->geom(), p->d_tab1, p->cut->rows, p->d_wcount, p->d_status, st));
     unsigned long long h[NLIVE_COUNTS];
     HIPCHK(hipMemcpyAsync(h, p->d_wcount, sizeof(h), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -1413,13 +1501,8 @@ int celeste_work_counts(celeste_plan* p, const double* theta, int64_t* counts, h
 
 int celeste_total_elbo(celeste_plan* p, const double* theta, double* out, hipStream_t st) {
     if (!p || !theta || !out) return CELESTE_EINVAL;
-    const Scope sc = scope_all(p);
-    CHK(validate_theta(p, theta, nullptr, nullptr, p->n_src, st));
-    CHK(prep(p, theta, sc.pair, false, DIR_NONE, nullptr, 0, st));
-    CHK(render(p, st, true));
-    HIPCHK(launch_tile_total(p->d_tile_sums, (int)p->tiles.size(), theta, p->consts, p->n_src, p->d_tt_part, out,
-                             p->d_status, st));
-    return CELESTE_OK;
+    const UseCut use(p, p->cut_eval);
+    return total_sequence(p, theta, out, st);
 }
 
 int celeste_newton(celeste_plan* p, double* theta, const int32_t* src, int n, int n_steps,
@@ -1433,6 +1516,7 @@ int celeste_newton(celeste_plan* p, double* theta, const int32_t* src, int n, in
         if (src[j] < 0 || src[j] >= p->n_src || seen[src[j]]) return CELESTE_EINVAL;
         seen[src[j]] = 1;
     }
+    const UseCut use(p, p->cut_newton);
     HostScope hs;
     scope_lists(p, src, n, hs);
     // with the strip render, the own profile values of the boxes the listed visits' backgrounds
@@ -1630,6 +1714,7 @@ int celeste_sweep(celeste_plan* p, double* theta, const int32_t* batch_ptr, cons
                 }
         }
     }
+    const UseCut use(p, p->cut_newton);   // the totals' strip passes too: later batches read their values
     // all batches' lists, concatenated
     HostScope hs;
     std::vector<int32_t> off_src(n_batches + 1), off_pair(n_batches + 1), off_item(n_batches + 1);
@@ -1686,10 +1771,10 @@ int celeste_sweep(celeste_plan* p, double* theta, const int32_t* batch_ptr, cons
             CHK(newton_run(p, theta, ss, sp, si, prm->newton_steps, prm, p->d_radius, s, stored));
             if (!stored) continue;
             CHK(prep(p, theta, sp, false, DIR_NONE, nullptr, 0, s));
-            HIPCHK(launch_strip_fg(si, p->geom(), p->d_tab1, p->d_fg, p->rows, p->launch_grid(), p->wpb,
+            HIPCHK(launch_strip_fg(si, p->geom(), p->d_tab1, p->d_fg, p->cut->rows, p->launch_grid(), p->wpb,
                                    p->d_status, s));
         }
-        if (!stored) return celeste_total_elbo(p, theta, total, s);
+        if (!stored) return total_sequence(p, theta, total, s);
         // every box's stored own values and coefficients are current: the total needs the
         // gather only, not the strip pass
         CHK(gather(p, true, s));
@@ -1697,7 +1782,7 @@ int celeste_sweep(celeste_plan* p, double* theta, const int32_t* batch_ptr, cons
                                  p->d_status, s));
         return CELESTE_OK;
     };
-    CHK(celeste_total_elbo(p, theta, elbo_trace, st));
+    CHK(total_sequence(p, theta, elbo_trace, st));
     if (!p->use_graph || n_sweeps == 0) {
         for (int sw = 0; sw < n_sweeps; ++sw) CHK(one_sweep(elbo_trace + sw + 1, st));
         return CELESTE_OK;
@@ -1764,7 +1849,7 @@ int celeste_autotune(celeste_plan* p, const double* theta, int reps, double* bes
         return CELESTE_OK;
     };
     struct Cfg { int chunk, wpb, grid, dyn, th, tw, rows, rmode; };
-    Cfg best{p->chunk, p->wpb, p->launch_grid(), p->dynamic, p->tile_h, p->tile_w, p->rows, p->render_mode};
+    Cfg best{p->chunk, p->wpb, p->launch_grid(), p->dynamic, p->tile_h, p->tile_w, p->cuts[0].rows, p->render_mode};
     double best_t = 1e300;
     int rc = celeste_plan_set_launch(p, best.chunk, best.wpb, best.grid, best.dyn, best.th, best.tw, best.rows,
                                      best.rmode);

@@ -127,3 +127,46 @@ def test_row_factors_at_the_psf_limit(B, O, synth, eig, rows):
         assert np.all(np.abs(g[s, :27] - gref) <= REL * np.abs(gref) + FLOOR * gabs), s
         Href, Habs = O.source_hessian(P, s, with_abs=True)
         assert np.all(np.abs(H[s] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
+
+
+# items of 16, 8 and 4 rows: 5, 5, 10; 90, 150, 275; 285, 495, 910; 520, 940, 1730; 850, 1485, 2800;
+# 20380, 36485, 67880 (at most 1024: one wave per SIMD; at most 16384: 16)
+@pytest.mark.parametrize("S,side,rows_eval,rows_newton", [(1, 60, 4, 4), (8, 160, 4, 4), (20, 200, 4, 4),
+                                                          (30, 240, 8, 8), (50, 300, 16, 8),
+                                                          (1100, 1000, 16, 16)])
+def test_a_new_plan_takes_the_strip_height_of_its_size(B, synth, S, side, rows_eval, rows_newton):
+    """A new plan's evaluations and its Newton, Hessian and sweep passes equal, bit for bit,
+    those of a plan set to the height that the plan's size calls for; its reported items stay
+    those of 16 rows, and setting the launch sets every pass."""
+    f = synth.sdss_field(S, H=side, W=side, seed=353)
+    new, ev, nt = B.Plan(f), B.Plan(f), B.Plan(f)
+    assert new.info()["strip_rows"] == 16
+    say("strip heights", S, "sources", new.info()["n_items"], "items")
+    ev.set_launch(strip_rows=rows_eval)
+    nt.set_launch(strip_rows=rows_newton)
+    th = device(f.theta)
+    v = device(np.random.default_rng(5).standard_normal(f.theta.shape))
+    act = torch.zeros(S, dtype=torch.uint8, device="cuda")
+    act[: (S + 1) // 2] = 1
+    src = np.arange(0, S, 1 + S // 20, dtype=np.int32)
+
+    def evaluations(p):
+        out = [*p.elbo_grad(th), *p.elbo_grad_noalloc(th, active=act), p.elbo(th, active=act),
+               p.total_elbo(th)]
+        if S < 100:
+            out += p.elbo_grad(th, mode=B.CELESTE_PLAIN)
+        return out + list(p.hvp(th, v, with_grad=True))
+
+    def steps(p):
+        t = th.clone()
+        e, r = p.newton(t, src, 2)
+        t2 = th.clone()
+        bp, bs = p.color_batches(3)
+        return [p.hessian(th, src), t, e, r, p.sweep(t2, bp, bs, 1, B.tr_params(newton_steps=1)), t2]
+
+    for a, b in zip(evaluations(new) + steps(new), evaluations(ev) + steps(nt)):
+        np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+    new.set_launch()
+    ev.set_launch()
+    for a, b in zip(evaluations(new) + steps(new), evaluations(ev) + steps(ev)):
+        np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
