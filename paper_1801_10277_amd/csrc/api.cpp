@@ -601,7 +601,7 @@ int render_tiles(celeste_plan* p, bool sums, hipStream_t st) {
     return CELESTE_OK;
 }
 
-// Planes (and with `sums` the per-tile ELBO sums) gathered from every box's stored own
+// Planes (with `sums` the per-tile ELBO sums instead) gathered from every box's stored own
 // profile values and brightness coefficients, which must be current.
 int gather(celeste_plan* p, bool sums, hipStream_t st) {
     RenderArgs a{};
@@ -624,7 +624,8 @@ int gather(celeste_plan* p, bool sums, hipStream_t st) {
 // E and V planes of all sources.  Mode 2: every box's own profile values (one parallel
 // strip pass), then a tile gather; mode 1: tiles evaluate the Gaussians; mode 0: sky fill,
 // then one strip launch per conflict-free class.  sums: also the per-tile sums of the
-// pixel terms of covered pixels into d_tile_sums (modes 0 and 1 then use the tiles).
+// pixel terms of covered pixels into d_tile_sums (modes 0 and 1 then use the tiles; modes 2
+// and 3 leave the planes as they were).
 int render(celeste_plan* p, hipStream_t st, bool sums = false) {
     p->fg_valid = false;
     if (p->render_mode == 1 || (sums && p->render_mode == 0)) return render_tiles(p, sums, st);

@@ -1946,6 +1946,11 @@ __global__ void __launch_bounds__(64) k_live_counts(Sel sel, const Item* __restr
 // Render pass 2: E and V of every pixel of a tile, summing the stored own values of the
 // tile's boxes in ascending box order (deterministic, no atomics).  Tile = (64 / tile_w * RP)
 // rows x tile_w columns; lane l owns rows l / tile_w + k (64 / tile_w), k < RP.
+// SUMS: the pixel terms of covered pixels summed per tile instead of the planes, which the
+// total ELBO alone does not read.  The kernel runs at the rate of its loads and stores; on
+// the 2000-source field the sums took 234 us with the planes written as well and a division
+// per pixel, without them and with the reciprocal's Newton steps 194 (the table log instead
+// of the library's: 192, not worth its block's table load).
 template <int RP, bool SUMS>
 __global__ void __launch_bounds__(256) k_gather_planes(RenderArgs a, const TileDev* __restrict__ tiles,
                                                        const int32_t* __restrict__ tile_list,
@@ -2029,13 +2034,15 @@ __global__ void __launch_bounds__(256) k_gather_planes(RenderArgs a, const TileD
     for (int k = 0; k < RP; ++k) {
         if (r[k] >= im.H || c >= im.W) continue;
         const size_t gi = (size_t)im.pix_offset + (size_t)r[k] * im.W + c;
-        Eout[gi] = E[k];
-        Vout[gi] = V[k];
-        if constexpr (SUMS) {
+        if constexpr (!SUMS) {
+            Eout[gi] = E[k];
+            Vout[gi] = V[k];
+        } else {
             // pixel term of a pixel some box covers (the total ELBO counts each such pixel once)
             const double x = xs[gi];
             if (covered[k] && x == x) {
-                double lk = x * (log(E[k]) - 0.5 * V[k] / (E[k] * E[k])) - E[k];
+                const double inv = frcp(E[k]);
+                double lk = x * (log(E[k]) - 0.5 * (V[k] * inv * inv)) - E[k];
                 if (a.g.consts.flags & CELESTE_INCLUDE_LGAMMA) lk -= lgamma(x + 1.0);
                 l += lk;
             }
