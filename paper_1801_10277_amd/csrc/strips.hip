@@ -239,15 +239,16 @@ constexpr int NQ = 8;   // row factors per component (L / 2 of them are used)
 
 // One wave writes the row factors of a box's components into its LDS slot [NCP][NQ] (0 for the
 // zero component): q_j+1 = q_j rho^(j+1), rho = exp(-d).
-__device__ __forceinline__ void stage_rows(const double* __restrict__ tab, double* myq, int lane,
+template <class T>
+__device__ __forceinline__ void stage_rows(const T* __restrict__ tab, double* myq, int lane,
                                            const double* __restrict__ t2) {
     if (lane > NCOMP) return;
     double q[NQ];
     if (lane < NCOMP) {
-        const double* e = tab + lane * CST;
-        const double rho = e[F_RDY];
+        const T* e = tab + lane * CST;
+        const double rho = value_of(e[F_RDY]);
         double pw = rho;
-        q[0] = fexp(-0.125 * e[F_PYY], t2);
+        q[0] = fexp(-0.125 * value_of(e[F_PYY]), t2);
 #pragma unroll
         for (int j = 1; j < NQ; ++j) {
             q[j] = q[j - 1] * pw;
@@ -654,13 +655,14 @@ __device__ __forceinline__ void strip_adjoint_q(const double* __restrict__ lt, c
 // Pixel term of one row: accumulates the value and d/dk1..k4 and returns the row
 // weights d l / d f_star and d l / d f_gal.
 // (The -log(x!) constant is not added here: each box's sum of it is precomputed once.)
-template <class T, bool DERIV>
+// VALUE: the value too.
+template <class T, bool DERIV, bool VALUE = true>
 __device__ __forceinline__ void strip_pixel(double x, T E, T V, T fs, T fg, const T* k, T* acc, T& Gs, T& Gg,
                                             const double2* __restrict__ tl) {
     const T Es = k[C_K1] * fs + k[C_K2] * fg;
     const T inv = frcp(E);
     const T r = V * inv * inv;
-    acc[A_VAL] += x * (flog(E, tl) - 0.5 * r) - E;
+    if (VALUE) acc[A_VAL] += x * (flog(E, tl) - 0.5 * r) - E;
     if (DERIV) {
         const T lE = x * inv * (1.0 + r) - 1.0;
         const T lV = -0.5 * x * (inv * inv);
@@ -971,6 +973,313 @@ __global__ void __launch_bounds__(256, 3) k_adjoint_stored(AdjArgs a, const Item
             int f;
             const double s = wave_sums_dealt<NACC>(acc, lane, f);
             if (f >= 0) partials[(size_t)ii * NACC + f] = s;
+        }
+        j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
+    }
+}
+
+// ------------------------------------------------------------- tangent over stored values
+// Gradient and tangent of a box's pixel sum along the direction in the tangent table, over
+// stored own profile values (Hessian-vector products).  A component's tangent is its value
+// times that of its logarithm, which down a strip is a quadratic in the row offset kappa from
+// the centre row: n'_k = n_k (C0 + kappa (C1 + kappa C2)).  So the rows need the values only,
+// by the row factors: the own profiles' tangents take 4.5 operations a row and component
+// (their values are the stored ones), the adjoint 11: with w = G' + G lambda the tangents of the
+// moments are the moments of w n, so two Horner schemes run side by side (strip_adjoint_q).
+// In dual numbers the row recurrences took 11 and 15, with the values evaluated again, and the
+// table came through the scalar cache: 1250 us on 1024 sources (1.6e7 visits), this 980 (the
+// row weights and their tangents take 128 registers of 16-row strips, two waves a SIMD; a pair
+// of seeds at a time spills, and takes as long).
+// Staged table [NTF][NCP] of (value, tangent), then the row factors [NCP][NQ].
+enum TangentField { T_CX = 0, T_CY, T_LW, T_A, T_B, T_D, T_WT, T_WNU, T_SGN, NTF };
+constexpr int STAGED_T = 2 * NCP * NTF + NCP * NQ;   // doubles of LDS per wave
+
+__device__ __forceinline__ dual dmul(dual a, dual b) { return mkd(a.v * b.v, fma(a.t, b.v, a.v * b.t)); }
+__device__ __forceinline__ dual dfma(dual a, dual b, dual c) {
+    return mkd(fma(a.v, b.v, c.v), fma(a.t, b.v, fma(a.v, b.t, c.t)));
+}
+
+__device__ __forceinline__ void stage_tangent(const dual* __restrict__ tab, dual* my, int lane) {
+    constexpr int from[NTF] = {F_CX, F_CY, F_LOGW, F_PXX, F_PXY, F_PYY, F_WT, F_WNU, F_SGN};
+    if (lane > NCOMP) return;
+    dual* o = my + (lane < NCOMP ? staged_slot(lane) : NPSF);
+#pragma unroll
+    for (int f = 0; f < NTF; ++f)
+        o[f * NCP] = lane < NCOMP ? tab[lane * CST + from[f]] : mkd(f == T_LW ? -1000.0 : 0.0);
+}
+
+// A strip in its PSF group's frame: the offsets of its column and centre row from the group's
+// centre, with their tangents (the same in every lane).
+struct TFrame {
+    double dx, dy, dxt, dyt;
+};
+template <int L>
+__device__ __forceinline__ TFrame tangent_frame(const dual* __restrict__ es, double px, double py0) {
+    const dual cx = es[T_CX * NCP], cy = es[T_CY * NCP];
+    TFrame f;
+    f.dx = px - cx.v;
+    f.dy = py0 + 0.5 * (L - 1) - cy.v;
+    f.dxt = -lane_bcast(cx.t, 0);
+    f.dyt = -lane_bcast(cy.t, 0);
+    return f;
+}
+
+// N0 and r of N components (the form of strip_values_q) and the quadratics of their
+// logarithms' tangents.
+template <int L, int N>
+__device__ __forceinline__ void seed_t(const dual* const* e, const TFrame& f, double* n, double* r, double (*c)[3],
+                                       const double* __restrict__ t2) {
+    constexpr double KC = 0.5 * (L - 1);
+    double x[2 * N], o[2 * N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const dual a = e[i][T_A * NCP], b = e[i][T_B * NCP], d = e[i][T_D * NCP], lw = e[i][T_LW * NCP];
+        const double zx = fma(a.v, f.dx, b.v * f.dy), zy = fma(b.v, f.dx, d.v * f.dy);
+        const double tx = fma(a.t, f.dx, b.t * f.dy), ty = fma(b.t, f.dx, d.t * f.dy);
+        x[i] = fma(KC, zy, fma(-0.5, fma(f.dx, zx, f.dy * zy), lw.v));
+        x[N + i] = fmin(-zy, LOG_R_MAX);
+        c[i][0] = fma(-0.5, fma(f.dx, tx, f.dy * ty), lw.t) - fma(zx, f.dxt, zy * f.dyt);
+        c[i][1] = -ty - fma(b.v, f.dxt, d.v * f.dyt);
+        c[i][2] = -0.5 * d.t;
+    }
+    fexps<2 * N>(x, o, t2);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        n[i] = o[i];
+        r[i] = o[N + i];
+    }
+}
+
+// Tangents of the own profile values down the strip.
+template <int L>
+__device__ __forceinline__ void strip_tangents_q(const dual* __restrict__ lt, const double* __restrict__ lq, double px,
+                                                 double py0, double* fst, double* fgt, const double* __restrict__ t2,
+                                                 uint64_t live) {
+    constexpr double KC = 0.5 * (L - 1);
+#pragma unroll
+    for (int k = 0; k < L; ++k) fst[k] = fgt[k] = 0.0;
+    auto rows = [&](int slot, double p, double r, double c0, double c1, double c2, double* f) {
+        double q[NQ], ev[L / 2];
+        load_rows<L>(lq + slot * NQ, q);
+#pragma unroll
+        for (int j = 0; j < L / 2; ++j) ev[j] = fma((j + 0.5) * (j + 0.5), c2, c0);
+#pragma unroll
+        for (int k = 0; k < L; ++k) {
+            f[k] = fma(q[row_q<L>(k)] * p, fma(k - KC, c1, ev[row_q<L>(k)]), f[k]);
+            if (k + 1 < L) p *= r;
+        }
+    };
+#pragma unroll 1
+    for (int grp = 0; grp < NPSF; ++grp) {
+        const bool star = (live >> grp) & 1;
+        if (!star && !((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
+        const TFrame f = tangent_frame<L>(lt + grp, px, py0);
+        if (star) {
+            const dual* e[1] = {lt + grp};
+            double n, r, c[1][3];
+            seed_t<L, 1>(e, f, &n, &r, c, t2);
+            rows(grp, n, r, c[0][0], c[0][1], c[0][2], fst);
+        }
+        for_live_pairs(live, grp, [&](int s0, int s1) {
+            const dual* e[2] = {lt + s0, lt + s1};
+            double n[2], r[2], c[2][3];
+            seed_t<L, 2>(e, f, n, r, c, t2);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                // the weight (de Vaucouleurs / exponential share) and its tangent
+                const dual w = e[i][T_WT * NCP];
+                rows(i ? s1 : s0, n[i], r[i], fma(w.v, c[i][0], w.t), w.v * c[i][1], w.v * c[i][2], fgt);
+            }
+        });
+    }
+}
+
+// strip_adjoint_q with tangents: row weights Gs, Gg with their tangents Gst, Ggt.
+template <int L>
+__device__ __forceinline__ void strip_adjoint_t(const dual* __restrict__ lt, const double* __restrict__ lq, double px,
+                                                double py0, const double* Gs, const double* Gst, const double* Gg,
+                                                const double* Ggt, dual* acc, const double* __restrict__ t2,
+                                                uint64_t live) {
+    constexpr double KC = 0.5 * (L - 1);
+#pragma unroll 1
+    for (int grp = 0; grp < NPSF; ++grp) {
+        const bool star = (live >> grp) & 1;
+        if (!star && !((live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1))) continue;
+        const TFrame f = tangent_frame<L>(lt + grp, px, py0);
+        const dual dx = mkd(f.dx, f.dxt), dy = mkd(f.dy - KC, f.dyt);   // the top row's
+        if (star) {
+            const dual* e = lt + grp;
+            double n, r, c[1][3], q[NQ];
+            seed_t<L, 1>(&e, f, &n, &r, c, t2);
+            load_rows<L>(lq + grp * NQ, q);
+            double h1 = 0.0, h0 = 0.0, g1 = 0.0, g0 = 0.0;
+#pragma unroll
+            for (int k = L - 1; k >= 0; --k) {
+                const double lam = fma(k - KC, fma(k - KC, c[0][2], c[0][1]), c[0][0]), qk = q[row_q<L>(k)];
+                h1 = fma(h1, r, h0);
+                h0 = fma(h0, r, Gs[k] * qk);
+                g1 = fma(g1, r, g0);
+                g0 = fma(g0, r, fma(Gs[k], lam, Gst[k]) * qk);
+            }
+            const dual a = e[T_A * NCP], b = e[T_B * NCP], d = e[T_D * NCP];
+            const double nr = n * r;
+            const dual M0 = mkd(n * h0, n * g0), M1 = dfma(dy, M0, mkd(nr * h1, nr * g1)), X1 = dmul(dx, M0);
+            acc[A_UX] = dfma(a, X1, dfma(b, M1, acc[A_UX]));
+            acc[A_UY] = dfma(b, X1, dfma(d, M1, acc[A_UY]));
+        }
+        uint32_t gm = (uint32_t)(live >> (NPSF + grp * NGAL_PER_PSF)) & ((1u << NGAL_PER_PSF) - 1);
+        while (gm) {
+            const int slot = NPSF + 1 + grp * NGAL_PER_PSF + __builtin_ctz(gm);
+            gm &= gm - 1;
+            const dual* e = lt + slot;
+            double n, r, c[1][3], q[NQ];
+            seed_t<L, 1>(&e, f, &n, &r, c, t2);
+            load_rows<L>(lq + slot * NQ, q);
+            double h2 = 0.0, h1 = 0.0, h0 = 0.0, g2 = 0.0, g1 = 0.0, g0 = 0.0;
+#pragma unroll
+            for (int k = L - 1; k >= 0; --k) {
+                const double lam = fma(k - KC, fma(k - KC, c[0][2], c[0][1]), c[0][0]), qk = q[row_q<L>(k)];
+                h2 = fma(h2, r, h1);
+                h1 = fma(h1, r, h0);
+                h0 = fma(h0, r, Gg[k] * qk);
+                g2 = fma(g2, r, g1);
+                g1 = fma(g1, r, g0);
+                g0 = fma(g0, r, fma(Gg[k], lam, Ggt[k]) * qk);
+            }
+            const dual a = e[T_A * NCP], b = e[T_B * NCP], d = e[T_D * NCP];
+            const double nr = n * r, nr2 = 2.0 * (nr * r);
+            const dual A = mkd(n * h0, n * g0), m1 = mkd(nr * h1, nr * g1), m2 = mkd(nr2 * h2, nr2 * g2);
+            const dual M1 = dfma(dy, A, m1), M2 = dfma(dy, M1 + m1, m1 + m2);
+            const dual X1 = dmul(dx, A), Y1 = dmul(dx, M1);
+            const dual U = dfma(a, X1, dmul(b, M1)), Up = dfma(b, X1, dmul(d, M1));
+            const dual W = dfma(a, Y1, dmul(b, M2)), Wp = dfma(b, Y1, dmul(d, M2));
+            const dual dU = dfma(dx, U, -A), dUp = dmul(dx, Up), Wm = Wp - A;
+            const dual wt = e[T_WT * NCP], wnu = e[T_WNU * NCP];
+            const dual wna = dmul(wnu, a), wnb = dmul(wnu, b), wnd = dmul(wnu, d);
+            const double sgn = e[T_SGN * NCP].v;
+            acc[A_FDEV] = mkd(fma(sgn, A.v, acc[A_FDEV].v), fma(sgn, A.t, acc[A_FDEV].t));
+            acc[A_UX] = dfma(wt, U, acc[A_UX]);
+            acc[A_UY] = dfma(wt, Up, acc[A_UY]);
+            acc[A_SXX] = dfma(wna, dU, dfma(wnb, W, acc[A_SXX]));
+            acc[A_SXY] = dfma(wnb, dU, dfma(wnd, W, acc[A_SXY]));
+            acc[A_SYY] = dfma(wnb, dUp, dfma(wnd, Wm, acc[A_SYY]));
+        }
+    }
+}
+
+// The pass itself, one wave per work item, rows loaded as in k_adjoint_stored.  (No value: the
+// tangent passes' callers do not read it.)
+template <int L>
+__global__ void __launch_bounds__(256, 2) k_tangent_stored(AdjArgs a, const Item* __restrict__ items,
+                                                           const PairDev* __restrict__ pairs,
+                                                           const celeste_image* __restrict__ images,
+                                                           const double* __restrict__ xs,
+                                                           const double* __restrict__ Ep,
+                                                           const double* __restrict__ Vp,
+                                                           const dual* __restrict__ tabp,
+                                                           const dual* __restrict__ coefp,
+                                                           const uint8_t* __restrict__ active,
+                                                           const double* __restrict__ fgm,
+                                                           dual* __restrict__ partials) {
+    if (*a.status) return;
+    __shared__ double t2[EXP_TAB];
+    extern __shared__ double ltab[];   // [waves per block][STAGED_T], sized at launch
+    load_tables(t2, nullptr);
+    const int lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6;
+    const int nw = gridDim.x * wpb;
+    dual* my = reinterpret_cast<dual*>(ltab + (threadIdx.x >> 6) * STAGED_T);
+    double* myq = reinterpret_cast<double*>(my + NCP * NTF);
+    constexpr int RB = 2, NB = L / RB;   // rows per lot, lots
+    int j = a.dynamic ? next_item_s(a.counter, lane) : blockIdx.x * wpb + (threadIdx.x >> 6);
+    while (j < a.items.n) {
+        const int ii = __builtin_amdgcn_readfirstlane(sel_at(a.items, j));
+        const Item it = items[ii];
+        const PairDev p = pairs[it.pair];
+        if (!active || active[p.src]) {
+            const celeste_image& im = images[p.img];
+            const dual* tab = tabp + (size_t)it.pair * NCOMP * CST;
+            // the wave's previous item has finished reading its copy (in-order LDS)
+            __builtin_amdgcn_wave_barrier();
+            stage_tangent(tab, my, lane);
+            stage_rows(tab, myq, lane, t2);
+            const uint64_t live = item_live(tab, p, it, L, lane);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const char* xb = reinterpret_cast<const char*>(xs + im.pix_offset);
+            const char* eb = reinterpret_cast<const char*>(Ep + im.pix_offset);
+            const char* vb = reinterpret_cast<const char*>(Vp + im.pix_offset);
+            const char* fb = reinterpret_cast<const char*>(fgm + 2 * p.visit_off);
+            const uint32_t W8 = (uint32_t)im.W * 8u, w16 = (uint32_t)p.w * 16u;
+            const dual* kp = coefp + (size_t)it.pair * NCOEF;
+            const dual k[NCOEF] = {kp[0], kp[1], kp[2], kp[3]};
+            dual acc[NACC];
+#pragma unroll
+            for (int f = 0; f < NACC; ++f) acc[f] = mkd(0.0);
+            for (int q0 = 0; q0 < it.count; q0 += 64) {
+                // lanes without a strip take the last one's with every row masked
+                int c, r0, nrow;
+                strip_geometry(p, it.start + min(q0 + lane, it.count - 1), L, c, r0, nrow);
+                if (q0 + lane >= it.count) nrow = 0;
+                const uint32_t go = (uint32_t)(r0 * im.W + c) * 8u;
+                const uint32_t vo = (uint32_t)((r0 - p.r0) * p.w + (c - p.c0)) * 16u;
+                double x_[2][RB], e_[2][RB], v_[2][RB], s_[2][RB], g_[2][RB];
+                // lot b of the strip's rows (a row past the box: the strip's top row)
+                auto load = [&](int b) {
+#pragma unroll
+                    for (int i = 0; i < RB; ++i) {
+                        const int rr = b * RB + i, u = b & 1;
+                        const bool in = rr < nrow;
+                        const uint32_t gr = go + (in ? (uint32_t)rr * W8 : 0u);
+                        const uint32_t vr = vo + (in ? (uint32_t)rr * w16 : 0u);
+                        x_[u][i] = *reinterpret_cast<const double*>(xb + gr);
+                        e_[u][i] = *reinterpret_cast<const double*>(eb + gr);
+                        v_[u][i] = *reinterpret_cast<const double*>(vb + gr);
+                        const double2 sg = *reinterpret_cast<const double2*>(fb + vr);
+                        s_[u][i] = sg.x;
+                        g_[u][i] = sg.y;
+                    }
+                };
+                load(0);
+                if constexpr (NB > 1) load(1);
+                const double px = (double)c, py0 = (double)r0;
+                double Gs[L], Gst[L], Gg[L], Ggt[L];   // tangents of the own values first
+                strip_tangents_q<L>(my, myq, px, py0, Gst, Ggt, t2, live);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                    for (int i = 0; i < RB; ++i) {
+                        const int kk = b * RB + i, u = b & 1;
+                        dual gs = mkd(0.0), gg = mkd(0.0);
+                        if (kk < nrow && x_[u][i] == x_[u][i]) {
+                            const dual fs = mkd(s_[u][i], Gst[kk]), fg = mkd(g_[u][i], Ggt[kk]);
+                            const dual Es = k[C_K1] * fs + k[C_K2] * fg;
+                            const dual Vs = k[C_K3] * (fs * fs) + k[C_K4] * (fg * fg) - Es * Es;
+                            strip_pixel<dual, true, false>(x_[u][i], value_with_tangent(e_[u][i], Es),
+                                                           value_with_tangent(v_[u][i], Vs), fs, fg, k, acc, gs, gg,
+                                                           nullptr);
+                        }
+                        Gs[kk] = gs.v;
+                        Gst[kk] = gs.t;
+                        Gg[kk] = gg.v;
+                        Ggt[kk] = gg.t;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (b + 2 < NB) load(b + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                strip_adjoint_t<L>(my, myq, px, py0, Gs, Gst, Gg, Ggt, acc, t2, live);
+            }
+            double v[2 * NACC];
+#pragma unroll
+            for (int f = 0; f < NACC; ++f) {
+                v[2 * f] = acc[f].v;
+                v[2 * f + 1] = acc[f].t;
+            }
+            int f;
+            const double s = wave_sums_dealt<2 * NACC>(v, lane, f);
+            if (f >= 0) reinterpret_cast<double*>(partials)[(size_t)ii * 2 * NACC + f] = s;
         }
         j = a.dynamic ? next_item_s(a.counter, lane) : j + nw;
     }
@@ -2209,6 +2518,16 @@ static hipError_t adjs(const AdjArgs& a, int grid, int wpb, hipStream_t st) {
             } else {
                 adjk<T, BASE, DERIV, L, true, KK_NONE>(a, grid, wpb, st);
             }
+            return hipSuccess;
+        }
+    }
+    if constexpr (!is_double && DERIV && BASE == BASE_PLANES) {
+        // tangents over the render's stored values, where the row factors may be taken
+        const Geometry& g = a.g;
+        if (a.fg && g.smooth) {
+            hipLaunchKernelGGL((k_tangent_stored<L>), dim3(grid), dim3(64 * wpb), (size_t)wpb * STAGED_T * sizeof(double),
+                               st, a, g.items, g.pairs, g.images, g.x, a.E, a.V, reinterpret_cast<const dual*>(a.tab),
+                               reinterpret_cast<const dual*>(a.coef), a.active, a.fg, reinterpret_cast<dual*>(a.partials));
             return hipSuccess;
         }
     }

@@ -170,3 +170,29 @@ def test_a_new_plan_takes_the_strip_height_of_its_size(B, synth, S, side, rows_e
     ev.set_launch()
     for a, b in zip(evaluations(new) + steps(new), evaluations(ev) + steps(ev)):
         np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+@pytest.mark.parametrize("rows,chunk,dynamic", [(4, 64, 0), (8, 192, 1), (16, 64, 0), (16, 1024, 1)])
+@pytest.mark.parametrize("eig,mode", [((0.66, 0.66), 2), ((0.667, 0.667), 2), ((0.667, 4.0), 2), ((9.0, 9.0), 2),
+                                      ((9.0, 9.0), 1)])
+def test_hvp_over_stored_values(B, O, synth, eig, mode, rows, chunk, dynamic):
+    """Hessian-vector products at the edges of the tangent pass over stored values (PSF
+    eigenvalues from 2/3 px^2, the render that stores them) and of the recurrence it leaves
+    the rest to: gradient and product per entry, boxes with a last strip of one row, items of
+    one strip per lane and of several, one unmasked and one masked pixel."""
+    f = synth.tiny(S=3, n_bands=2, size=71, side=49, seed=359)
+    a, b = eig
+    f.img_psf[:, :, 3] = f.img_psf[:, :, 5] = 0.5 * (a + b)
+    f.img_psf[:, :, 4] = 0.5 * (b - a)
+    f.x[37::211] = np.nan
+    plan, P = B.Plan(f), O.Problem(f)
+    plan.set_launch(strip_rows=rows, chunk=chunk, dynamic=dynamic, render_mode=mode)
+    v = np.random.default_rng(11).standard_normal(f.theta.shape)
+    say("hvp stored", eig, mode, rows, chunk)
+    hv, g = (t.cpu().numpy() for t in plan.hvp(device(f.theta), device(v), with_grad=True))
+    for s in range(3):
+        _, gref, gabs = O.source_grad(P, s)
+        href, habs = O.source_hvp(P, s, v[s])
+        n = len(gref)
+        assert np.all(np.abs(g[s, :n] - gref) <= REL * np.abs(gref) + FLOOR * gabs), s
+        assert np.all(np.abs(hv[s, :n] - href) <= REL * np.abs(href) + FLOOR * habs), s
