@@ -343,7 +343,8 @@ int celeste_sweep(celeste_plan* plan, double* theta_inout, const int32_t* batch_
  * plan starts at chunk 64, 4 waves per block, grid 0, static queue, 16 x 16 tiles, 16-row
  * strips, render mode 2; until this is called, the passes of a plan too small to fill the
  * device with 16-row strips take lower ones (the plan's items, and info, stay the 16-row
- * ones).  Afterwards every pass takes strip_rows.  Rebuilds work items and render tiles
+ * ones), and some passes over many items take blocks of one wave.  Afterwards every pass
+ * takes strip_rows and waves_per_block.  Rebuilds work items and render tiles
  * (synchronous).  If grown tile buffers cannot be allocated it returns CELESTE_ENOMEM and
  * the plan keeps its previous configuration. */
 int celeste_plan_set_launch(celeste_plan* plan, int chunk, int waves_per_block, int grid_blocks,

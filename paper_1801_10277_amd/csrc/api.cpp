@@ -56,7 +56,7 @@ struct Cut {
     int rows = 16;
     std::vector<Item> items;
     std::vector<int32_t> ptr;    // [n_pairs + 1] first item of each box
-    Item* d_items = nullptr;
+    Item* d_items = nullptr;     // in the plan's
     PairDev* d_pairs = nullptr;  // the boxes with their items
 };
 
@@ -77,6 +77,7 @@ struct celeste_plan {
 
     // launch configuration
     int chunk = 64, wpb = 4, grid = 0, dynamic = 0, tile_h = 16, tile_w = 16;
+    bool launch_set = false;   // celeste_plan_set_launch was called
     // 0: strips per conflict-free class, 1: binned tiles, 2: stored values + tile gather,
     // 3: stored values, background gathered inside the fused adjoint (no planes)
     int render_mode = 2;
@@ -88,6 +89,8 @@ struct celeste_plan {
 
     // device memory
     celeste_image* d_images = nullptr;
+    PairDev* d_pairs = nullptr;      // every cut's
+    Item* d_items = nullptr;
     int32_t* d_nbr = nullptr;
     TileDev* d_tiles = nullptr;
     size_t cap_tiles = 0;
@@ -177,6 +180,16 @@ struct celeste_plan {
         return g;
     }
     int64_t n_pairs() const { return (int64_t)pairs.size(); }
+    // Waves per block of the passes that fit two waves a SIMD (tangents, stored backgrounds,
+    // Hessian sums) over `items`, until the launch is set.  The waves of a block hold their
+    // registers until its slowest ends, so with more items than the device takes at once,
+    // blocks of one wave keep more of them busy; with fewer, blocks of four share their table
+    // loads: us a call with four / one (results do not depend on it),
+    //   product, 500 sources (9440 items)              572 / 546;  120 sources (2090)  219 / 197
+    //   3 Newton steps, 500 of 500 sources (16925)    3003 / 2845; 120 of 120 (3770)  1108 / 1061
+    //   3 Newton steps, 50 of 500 sources (~1700)      810 / 828;  50 of 50 (1510)     729 / 736
+    // The passes at three waves a SIMD do not care (2000-source gradient: 965 / 961).
+    int pass_wpb(const Sel& list) const { return launch_set || list.n <= 8 * n_cu ? wpb : 1; }
     int launch_grid() const { return grid > 0 ? grid : 64 * n_cu; }
 };
 
@@ -378,17 +391,46 @@ void build_nbr(celeste_plan* p) {
     }
 }
 
-int upload_geometry(celeste_plan* p) {
-    std::vector<PairDev> pairs(p->pairs);
-    for (const Cut& c : p->cuts) {
-        if (c.ptr.empty()) continue;   // not in use
-        for (size_t i = 0; i < pairs.size(); ++i) {
-            pairs[i].item_begin = c.ptr[i];
-            pairs[i].item_end = c.ptr[i + 1];
+// The cuts' boxes and items on the device, one block of each kind; cuts[0], which set_launch
+// rebuilds within max_items, comes last.
+int alloc_cuts(celeste_plan* p, size_t np, size_t max_items, size_t& W) {
+    size_t n = 0, extra = 0;
+    for (const Cut& c : p->cuts)
+        if (!c.ptr.empty()) {
+            ++n;
+            if (&c != &p->cuts[0]) extra += c.items.size();
         }
-        HIPCHK(hipMemcpy(c.d_pairs, pairs.data(), pairs.size() * sizeof(PairDev), hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(c.d_items, c.items.data(), c.items.size() * sizeof(Item), hipMemcpyHostToDevice));
+    int r = dalloc(&p->d_pairs, n * np, W);
+    if (r == CELESTE_OK) r = dalloc(&p->d_items, extra + max_items, W);
+    if (r != CELESTE_OK) return r;
+    PairDev* dp = p->d_pairs;
+    Item* di = p->d_items;
+    for (int k = 2; k >= 0; --k) {
+        Cut& c = p->cuts[k];
+        if (c.ptr.empty()) continue;
+        c.d_pairs = dp;
+        c.d_items = di;
+        dp += p->pairs.size();
+        di += c.items.size();
     }
+    return CELESTE_OK;
+}
+
+int upload_geometry(celeste_plan* p) {
+    std::vector<PairDev> pairs;
+    std::vector<Item> items;
+    for (int k = 2; k >= 0; --k) {   // as alloc_cuts lays them out
+        const Cut& c = p->cuts[k];
+        if (c.ptr.empty()) continue;
+        for (size_t i = 0; i < p->pairs.size(); ++i) {
+            pairs.push_back(p->pairs[i]);
+            pairs.back().item_begin = c.ptr[i];
+            pairs.back().item_end = c.ptr[i + 1];
+        }
+        items.insert(items.end(), c.items.begin(), c.items.end());
+    }
+    HIPCHK(hipMemcpy(p->d_pairs, pairs.data(), pairs.size() * sizeof(PairDev), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(p->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
     if (!p->cls_items.empty())
         HIPCHK(hipMemcpy(p->d_cls_items, p->cls_items.data(), p->cls_items.size() * sizeof(int32_t),
                          hipMemcpyHostToDevice));
@@ -679,7 +721,8 @@ int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tange
     }
     a.status = p->d_status;
     const int grid = grid_override > 0 ? grid_override : p->launch_grid();
-    HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, p->wpb, p->cut->rows, st));
+    const int wpb = tangent || base == BASE_BG ? p->pass_wpb(items) : p->wpb;
+    HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, wpb, p->cut->rows, st));
     return CELESTE_OK;
 }
 
@@ -953,7 +996,7 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.dynamic = p->dynamic;
         a.counter = p->d_counter;
         a.status = p->d_status;
-        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->wpb, p->cut->rows, st));
+        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->pass_wpb(item), p->cut->rows, st));
     }
     HIPCHK(launch_pair_block(pair, p->cut->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
                              p->d_hw, active, p->d_status, st));
@@ -1088,7 +1131,7 @@ void celeste_plan_destroy(celeste_plan* p) {
     if (p->h_stage) (void)hipHostFree(p->h_stage);
     if (p->stage_ev) (void)hipEventDestroy(p->stage_ev);
     if (p->sweep_ev) (void)hipEventDestroy(p->sweep_ev);
-    void* bufs[] = {p->d_images, p->d_nbr, p->d_tiles, p->d_tile_list, p->d_patch_ptr,
+    void* bufs[] = {p->d_images, p->d_pairs, p->d_items, p->d_nbr, p->d_tiles, p->d_tile_list, p->d_patch_ptr,
                     p->d_tab1, p->d_coef1, p->d_tab2, p->d_coef2, p->d_partials, p->d_E, p->d_V, p->d_bg,
                     p->d_tile_sums, p->d_status, p->d_counter, p->d_grad, p->d_hess, p->d_theta_trial,
                     p->d_pred, p->d_elbo_cur, p->d_elbo_trial, p->d_radius, p->d_done, p->d_list_src,
@@ -1097,10 +1140,6 @@ void celeste_plan_destroy(celeste_plan* p) {
                     p->d_mix, p->d_scalar, p->d_tt_part, p->d_list_npair, p->d_list_nitem, p->d_wcount};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
-    for (Cut& c : p->cuts) {
-        if (c.d_items) (void)hipFree(c.d_items);
-        if (c.d_pairs) (void)hipFree(c.d_pairs);
-    }
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     for (hipEvent_t& e : p->ev)
         if (e) (void)hipEventDestroy(e);
@@ -1180,11 +1219,7 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     int r = CELESTE_OK;
     auto A = [&](int rc) { if (rc != CELESTE_OK && r == CELESTE_OK) r = rc; };
     A(dalloc(&p->d_images, p->n_img, W));
-    for (Cut& c : p->cuts) {
-        if (c.ptr.empty()) continue;
-        A(dalloc(&c.d_pairs, np, W));
-        A(dalloc(&c.d_items, max_items, W));
-    }
+    A(alloc_cuts(p, np, max_items, W));
     A(dalloc(&p->d_nbr, std::max<size_t>(p->nbr.size(), 1), W));
     A(dalloc(&p->d_tiles, p->tiles.size(), W));
     p->cap_tiles = p->tiles.size();
@@ -1351,6 +1386,7 @@ int celeste_plan_set_launch(celeste_plan* p, int chunk, int wpb, int grid, int d
     }
     p->cuts[0].rows = strip_rows;
     p->cut_eval = p->cut_newton = &p->cuts[0];
+    p->launch_set = true;
     p->render_mode = render_mode;
     p->chunk = chunk;
     p->wpb = wpb;
