@@ -1424,7 +1424,7 @@ int celeste_plan_status(celeste_plan* p, hipStream_t st) {
     HIPCHK(hipStreamSynchronize(st));
     int s = 0;
     HIPCHK(hipMemcpy(&s, p->d_status, sizeof(int), hipMemcpyDeviceToHost));
-    HIPCHK(hipMemset(p->d_status, 0, sizeof(int)));
+    if (s) HIPCHK(hipMemset(p->d_status, 0, sizeof(int)));
     return s;
 }
 

@@ -196,3 +196,22 @@ def test_hvp_over_stored_values(B, O, synth, eig, mode, rows, chunk, dynamic):
         n = len(gref)
         assert np.all(np.abs(g[s, :n] - gref) <= REL * np.abs(gref) + FLOOR * gabs), s
         assert np.all(np.abs(hv[s, :n] - href) <= REL * np.abs(href) + FLOOR * habs), s
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 1024, 1025])
+def test_validation_of_lists_of_one_block_and_more(B, synth, n):
+    """A bad row of a listed source refuses the call wherever it stands in the list, one of an
+    unlisted source does not, and the next call starts with a clear status."""
+    f = synth.tiny(S=1030, n_bands=1, size=64, side=5, seed=367)
+    plan = B.Plan(f)
+    src = np.arange(n, dtype=np.int32)
+    say("validate", n)
+    for bad in (0, n - 1, 1029):
+        th = f.theta.copy()
+        th[bad, 6] = 1.5
+        if bad < n:
+            with pytest.raises(B.CelesteError):
+                plan.newton(device(th), src, 0)
+        else:
+            plan.newton(device(th), src, 0)
+        plan.newton(device(f.theta), src, 0)
