@@ -1579,10 +1579,12 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item
 // z is affine in the row: z_k = z_c + (b, d) s_k with z_c its value at the strip centre and
 // s_k = k - (L - 1)/2, so with the strip recurrence for n and the exact centred row moments
 // U_m = sum_k t_k s_k^m (t_k = row weight x value, m <= 4; s_k^m are compile-time constants)
-// the sums N_pq = sum_k t_k zx_k^p zy_k^q follow by applying the maps
-// (X V)_m = zx_c V_m + b V_(m+1) and (Y V)_m = zy_c V_m + d V_(m+1) to U: N_pq = (X^p Y^q U)_0.
+// the sums N_pq = sum_k t_k zx_k^p zy_k^q follow by two kinds of map: V_q = N_0q = (Y^q U)_0 with
+// (Y U)_m = zy_c U_m + d U_(m+1), and, zx = g + beta zy along the strip (beta = b / d,
+// g = (a - beta b) dx), N_pq = (X^p V)_q with (X V)_q = g V_q + beta V_(q+1): ten steps of each.
 // With the moments about the strip centre, every term of these expansions is bounded by the
-// strip's own values of |z|^4, so no cancellation beyond a small factor arises.  The entries
+// strip's own values of |z|^4 (beta zy by the bound of zx: b^2 < a d), so no cancellation
+// beyond a small factor arises.  The entries
 // (galaxy component, weights wt, sgn, wnu = wt nu):
 //   XX, XY, YY: wt (N20 - a N00, N11 - b N00, N02 - d N00);   XF, YF: sgn N10, sgn N01;
 //   F_Sxx, F_Sxy, F_Syy: sgn nu times the same three as XX, XY, YY;
@@ -1597,7 +1599,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item
 // (N20 - a N00, N11 - b N00, N02 - d N00); N10, N01 for a star.  One pass over the components per strip
 // (two exps per component), against one exp and about 55 operations per pixel and component
 // for the same terms pixel by pixel.
-enum HessStagedField { H_CX = 0, H_CY, H_LW, H_RDY, H_A, H_B, H_D, H_WT, H_WNU, H_SGN, H_NU, NDH };
+enum HessStagedField { H_CX = 0, H_CY, H_LW, H_RDY, H_A, H_B, H_D, H_WT, H_WNU, H_SGN, H_NU, H_BE, NDH };
 
 // One wave writes the staged table of a box (field-major [NDH][NCP], slots as in
 // stage_derived) into its LDS slot; nu[g]: nu of galaxy component g.
@@ -1617,6 +1619,7 @@ __device__ __forceinline__ void stage_hess(const double* __restrict__ tab, const
         o[H_WNU * NCP] = e[F_WNU];
         o[H_SGN * NCP] = e[F_SGN];
         o[H_NU * NCP] = lane < NPSF ? 0.0 : nu[lane - NPSF];
+        o[H_BE * NCP] = e[F_PXY] / e[F_PYY];
     } else if (lane == NCOMP) {   // the zero component (stage_derived)
         double* o = my + NPSF;
 #pragma unroll
@@ -1667,10 +1670,8 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             acc[A_UX - A_UX] += X10;
             acc[A_UY - A_UX] += Y10;
         }
-        auto gal = [&](const double* __restrict__ e) {
+        auto gal = [&](const double* __restrict__ e, double n, double rt) {
             const double a = e[H_A * NCP], b = e[H_B * NCP], d = e[H_D * NCP];
-            double n = fexp(fma(a, h2x, fma(b, mxy, fma(d, h2y, e[H_LW * NCP]))), t2);
-            double rt = fexp(clamp_arg(fma(b, mdx, d * mdyh)), t2);
             const double rdy = e[H_RDY * NCP];
             double U[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1687,8 +1688,8 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
                     rt = rt * rdy;
                 }
             }
-            const double zx = fma(a, dx, b * dyc), zy = fma(b, dx, d * dyc);
-            // Y^q U for q = 1..4, then X^p on each: N_pq = (X^p Y^q U)_0
+            // the maps of the head comment
+            const double zy = fma(b, dx, d * dyc), be = e[H_BE * NCP], g = fma(-be, b, a) * dx;
             double Y1[4], Y2[3], Y3[2];
 #pragma unroll
             for (int m = 0; m < 4; ++m) Y1[m] = fma(zy, U[m], d * U[m + 1]);
@@ -1696,23 +1697,12 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             for (int m = 0; m < 3; ++m) Y2[m] = fma(zy, Y1[m], d * Y1[m + 1]);
 #pragma unroll
             for (int m = 0; m < 2; ++m) Y3[m] = fma(zy, Y2[m], d * Y2[m + 1]);
-            const double N04 = fma(zy, Y3[0], d * Y3[1]);
-            double X1[4], X2[3], X3[2];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) X1[m] = fma(zx, U[m], b * U[m + 1]);
-#pragma unroll
-            for (int m = 0; m < 3; ++m) X2[m] = fma(zx, X1[m], b * X1[m + 1]);
-#pragma unroll
-            for (int m = 0; m < 2; ++m) X3[m] = fma(zx, X2[m], b * X2[m + 1]);
-            const double N40 = fma(zx, X3[0], b * X3[1]);
-            const double N00 = U[0], N10 = X1[0], N20 = X2[0], N30 = X3[0];
-            const double XY1a = fma(zx, Y1[0], b * Y1[1]), XY1b = fma(zx, Y1[1], b * Y1[2]),
-                         XY1c = fma(zx, Y1[2], b * Y1[3]);
-            const double XXY1a = fma(zx, XY1a, b * XY1b), XXY1b = fma(zx, XY1b, b * XY1c);
-            const double N01 = Y1[0], N11 = XY1a, N21 = XXY1a, N31 = fma(zx, XXY1a, b * XXY1b);
-            const double XY2a = fma(zx, Y2[0], b * Y2[1]), XY2b = fma(zx, Y2[1], b * Y2[2]);
-            const double N02 = Y2[0], N12 = XY2a, N22 = fma(zx, XY2a, b * XY2b);
-            const double N03 = Y3[0], N13 = fma(zx, Y3[0], b * Y3[1]);
+            const double N00 = U[0], N01 = Y1[0], N02 = Y2[0], N03 = Y3[0], N04 = fma(zy, Y3[0], d * Y3[1]);
+            const double N10 = fma(g, N00, be * N01), N11 = fma(g, N01, be * N02), N12 = fma(g, N02, be * N03),
+                         N13 = fma(g, N03, be * N04);
+            const double N20 = fma(g, N10, be * N11), N21 = fma(g, N11, be * N12), N22 = fma(g, N12, be * N13);
+            const double N30 = fma(g, N20, be * N21), N31 = fma(g, N21, be * N22);
+            const double N40 = fma(g, N30, be * N31);
             const double wt = e[H_WT * NCP], sg = e[H_SGN * NCP], wnu = e[H_WNU * NCP], nu = e[H_NU * NCP];
             const double snu = sg * nu, vnu = wnu * nu;
             const double e20 = fma(-a, N00, N20), e11 = fma(-b, N00, N11), e02 = fma(-d, N00, N02);
@@ -1736,9 +1726,7 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             const double x4 = fma(-3.0 * d, N01, N03);
             H[HG_X_SXX] = fma(wnu, x1, H[HG_X_SXX]);
             H[HG_X_SXY] = fma(wnu, x2, H[HG_X_SXY]);
-            H[HG_Y_SXX] = fma(wnu, x2, H[HG_Y_SXX]);
             H[HG_X_SYY] = fma(wnu, x3, H[HG_X_SYY]);
-            H[HG_Y_SXY] = fma(wnu, x3, H[HG_Y_SXY]);
             H[HG_Y_SYY] = fma(wnu, x4, H[HG_Y_SYY]);
             const double s1 = fma(-6.0 * a, N20, fma(3.0 * (a * a), N00, N40));
             const double s2 = fma(-3.0 * b, N20, fma(-3.0 * a, N11, fma(3.0 * (a * b), N00, N31)));
@@ -1748,13 +1736,14 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
             H[HG_SXX_SXX] = fma(vnu, s1, H[HG_SXX_SXX]);
             H[HG_SXX_SXY] = fma(vnu, s2, H[HG_SXX_SXY]);
             H[HG_SXX_SYY] = fma(vnu, s3, H[HG_SXX_SYY]);
-            H[HG_SXY_SXY] = fma(vnu, s3, H[HG_SXY_SXY]);
             H[HG_SXY_SYY] = fma(vnu, s4, H[HG_SXY_SYY]);
             H[HG_SYY_SYY] = fma(vnu, s5, H[HG_SYY_SYY]);
         };
         for_live_pairs(live, grp, [&](int s0, int s1) {
-            gal(lt + s0);
-            gal(lt + s1);
+            double n[2], rt[2];
+            seed_pair(lt + s0, lt + s1, h2x, mxy, h2y, mdx, mdyh, n, rt, t2);
+            gal(lt + s0, n[0], rt[0]);
+            gal(lt + s1, n[1], rt[1]);
         });
     }
 }
@@ -1764,11 +1753,13 @@ __device__ __forceinline__ void hess_second_strip(const double* __restrict__ lt,
 // Writes hg[item] (geometric entries; the k-block entries zero), to which k_hess_geom then
 // adds the first-derivative products, and the position, frac_dev and shape entries of
 // a.partials[item].  Items of sources outside a.active get zeros.
-// Three waves per SIMD (168 VGPRs, some spilled) rather than two (197 VGPRs): the waves wait
-// on each strip's row loads, and the third wave hides more of it (Newton iterations on 1024
-// sources 1.5% faster).
+// The rows come four at a time, loaded whether masked or not and the next four while these are
+// worked off: loaded each behind its pixel's mask, row after row, they were what a third wave
+// per SIMD was worth spilling 69 registers for.  Two waves unspilled have room for the seeds of
+// two components at a time.  1024 sources (1.6e7 visits): 532 us with masked loads and three
+// waves, 427 with lots of two rows, 415 with lots of four and paired seeds.
 template <int L>
-__global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* __restrict__ items,
+__global__ void __launch_bounds__(256, 2) k_hess_second(AdjArgs a, const Item* __restrict__ items,
                                                      const PairDev* __restrict__ pairs,
                                                      const celeste_image* __restrict__ images,
                                                      const double* __restrict__ xs, const double* __restrict__ bg,
@@ -1809,34 +1800,60 @@ __global__ void __launch_bounds__(256, 3) k_hess_second(AdjArgs a, const Item* _
         for (int f = 0; f < NHG_GEO; ++f) H[f] = 0.0;
 #pragma unroll
         for (int f = 0; f < NACC - A_UX; ++f) acc[f] = 0.0;
+        const double* xi = xs + im.pix_offset;
+        const double2* oi = reinterpret_cast<const double2*>(own) + p.visit_off;
+        const double2* bi = reinterpret_cast<const double2*>(bg) + p.visit_off;
+        constexpr int RB = L < 4 ? L : 4, NB = L / RB;   // rows per lot, lots
         for (int q = lane; q < it.count; q += 64) {
             int c, r0, nrow;
             strip_geometry(p, it.start + q, L, c, r0, nrow);
+            const uint32_t go = (uint32_t)(r0 * im.W + c), vo = (uint32_t)((r0 - p.r0) * p.w + (c - p.c0));
+            double x_[2][RB];
+            double2 o_[2][RB], b_[2][RB];
+            auto load = [&](int b) {
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    const int rr = b * RB + i < nrow ? b * RB + i : 0;   // rows past the box reuse row 0 (weight 0)
+                    x_[b & 1][i] = xi[go + (uint32_t)(rr * im.W)];
+                    o_[b & 1][i] = oi[vo + (uint32_t)(rr * p.w)];
+                    b_[b & 1][i] = bi[vo + (uint32_t)(rr * p.w)];
+                }
+            };
+            load(0);
+            if constexpr (NB > 1) load(1);
             double Gs[L], Gg[L];
 #pragma unroll
-            for (int kk = 0; kk < L; ++kk) {
-                const int r = r0 + (kk < nrow ? kk : 0);   // rows past the box reuse row 0 (weight 0)
-                const double x = xs[(size_t)im.pix_offset + (size_t)r * im.W + c];
-                const size_t vi = (size_t)p.visit_off + (size_t)(r - p.r0) * p.w + (c - p.c0);
-                double gs = 0.0, gg = 0.0;
-                if (kk < nrow && x == x) {
-                    const double fs = own[2 * vi], fgv = own[2 * vi + 1];
-                    const double Es = k1 * fs + k2 * fgv;
-                    const double E = bg[2 * vi] + Es;
-                    const double V = bg[2 * vi + 1] + k3 * (fs * fs) + k4 * (fgv * fgv) - Es * Es;
-                    const double inv = frcp(E);
-                    const double inv2 = inv * inv;
-                    const double lE = x * inv * (1.0 + V * inv2) - 1.0;
-                    const double lV = -0.5 * x * inv2;
-                    const double A = lE - 2.0 * Es * lV;
-                    gs = A * k1 + 2.0 * lV * (k3 * fs);
-                    gg = A * k2 + 2.0 * lV * (k4 * fgv);
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    const int kk = b * RB + i;
+                    const double x = x_[b & 1][i];
+                    double gs = 0.0, gg = 0.0;
+                    if (kk < nrow && x == x) {
+                        const double fs = o_[b & 1][i].x, fgv = o_[b & 1][i].y;
+                        const double Es = k1 * fs + k2 * fgv;
+                        const double E = b_[b & 1][i].x + Es;
+                        const double V = b_[b & 1][i].y + k3 * (fs * fs) + k4 * (fgv * fgv) - Es * Es;
+                        const double inv = frcp(E);
+                        const double inv2 = inv * inv;
+                        const double lE = x * inv * (1.0 + V * inv2) - 1.0;
+                        const double lV = -0.5 * x * inv2;
+                        const double A = lE - 2.0 * Es * lV;
+                        gs = A * k1 + 2.0 * lV * (k3 * fs);
+                        gg = A * k2 + 2.0 * lV * (k4 * fgv);
+                    }
+                    Gs[kk] = gs;
+                    Gg[kk] = gg;
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                Gs[kk] = gs;
-                Gg[kk] = gg;
+                if (b + 2 < NB) load(b + 2);
+                __builtin_amdgcn_sched_barrier(0);
             }
             hess_second_strip<L>(my, (double)c, (double)r0, Gs, Gg, H, acc, t2, live);
         }
+        H[HG_Y_SXX] = H[HG_X_SXY];   // the same sums
+        H[HG_Y_SXY] = H[HG_X_SYY];
+        H[HG_SXY_SXY] = H[HG_SXX_SYY];
         double v[NHG_GEO + NACC - A_UX];
 #pragma unroll
         for (int f = 0; f < NHG_GEO; ++f) v[f] = H[f];
