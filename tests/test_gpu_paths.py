@@ -215,3 +215,21 @@ def test_validation_of_lists_of_one_block_and_more(B, synth, n):
         else:
             plan.newton(device(th), src, 0)
         plan.newton(device(f.theta), src, 0)
+
+
+@pytest.mark.parametrize("S", [3, 64, 65, 66, 140])
+@pytest.mark.parametrize("rows,chunk", [(4, 64), (8, 192), (16, 64)])
+def test_backgrounds_of_crowded_boxes(B, O, synth, S, rows, chunk):
+    """Dense Hessians over stored backgrounds and the total ELBO where boxes meet up to one, two
+    and three waves' worth of other boxes, some on their edges only: each entry within its
+    gate of the oracle's."""
+    f = synth.tiny(S=S, n_bands=1, size=48, side=27, seed=373)
+    plan, P = B.Plan(f), O.Problem(f)
+    plan.set_launch(strip_rows=rows, chunk=chunk)
+    src = sorted({0, S // 2, S - 1})
+    say("crowded", S, "boxes", plan.info()["n_nbr"], "neighbours")
+    H = plan.hessian(device(f.theta), src).cpu().numpy()
+    for j, s in enumerate(src):
+        Href, Habs = O.source_hessian(P, s, with_abs=True)
+        assert np.all(np.abs(H[j] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
+    np.testing.assert_allclose(float(plan.total_elbo(device(f.theta))[0]), O.total_elbo(P), rtol=1e-11)
