@@ -129,12 +129,12 @@ struct celeste_plan {
     double* d_elbo_trial = nullptr;
     double* d_radius = nullptr;
     uint8_t* d_done = nullptr;
-    int32_t* d_list_src = nullptr;   // [n_src]
-    int32_t* d_list_pair = nullptr;  // [n_pairs]
-    int32_t* d_list_item = nullptr;  // [max_items]
-    int32_t* d_list_npair = nullptr; // [n_pairs] boxes whose stored values a Newton call renders
-    int32_t* d_list_nitem = nullptr; // [max_items] their items
-    size_t cap_list_item = 0, cap_list_src = 0, cap_list_pair = 0;
+    // a call's lists, one after the other in one buffer (upload): sources, boxes, items, and
+    // the boxes whose stored values the call renders with their items
+    int32_t* d_list = nullptr;       // [n_src + 2 n_pairs + 2 max_items], or what a sweep needed
+    size_t cap_list = 0;
+    const int32_t *d_list_src = nullptr, *d_list_pair = nullptr, *d_list_item = nullptr, *d_list_npair = nullptr,
+                  *d_list_nitem = nullptr;
     // conflict-free classes of boxes (no two boxes of a class share a pixel) and their items
     std::vector<int32_t> pair_class;
     int n_class = 0;
@@ -891,10 +891,11 @@ int fill_f64(double* d, const Sel& srcs, double v, hipStream_t st) {
     return CELESTE_OK;
 }
 
-// Host lists into device buffers on `st`, through the plan's pinned staging: no host
-// synchronisation except, when the staging is still being read by the previous upload, a
-// wait for that copy.  Growing the staging allocates pinned host memory.
-int upload(celeste_plan* p, std::initializer_list<std::pair<const std::vector<int32_t>*, int32_t*>> lists,
+// Host lists into d_list on `st`, through the plan's pinned staging and in one copy (one each
+// took 35 of 197 us of a call for 24 Hessians): no host synchronisation except, when the
+// staging is still being read by the previous upload, a wait for that copy.  Growing the
+// staging allocates pinned host memory.
+int upload(celeste_plan* p, std::initializer_list<std::pair<const std::vector<int32_t>*, const int32_t**>> lists,
            hipStream_t st) {
     size_t n = 0;
     for (const auto& l : lists) n += l.first->size();
@@ -912,18 +913,18 @@ int upload(celeste_plan* p, std::initializer_list<std::pair<const std::vector<in
     size_t off = 0;
     for (const auto& l : lists) {
         const std::vector<int32_t>& v = *l.first;
-        if (v.empty()) continue;
         std::copy(v.begin(), v.end(), p->h_stage + off);
-        HIPCHK(hipMemcpyAsync(l.second, p->h_stage + off, v.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+        *l.second = p->d_list + off;
         off += v.size();
     }
+    if (n) HIPCHK(hipMemcpyAsync(p->d_list, p->h_stage, n * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIPCHK(hipEventRecord(p->stage_ev, st));
     p->stage_pending = true;
     return CELESTE_OK;
 }
 
 int upload_lists(celeste_plan* p, const HostScope& hs, hipStream_t st) {
-    return upload(p, {{&hs.src, p->d_list_src}, {&hs.pair, p->d_list_pair}, {&hs.item, p->d_list_item}}, st);
+    return upload(p, {{&hs.src, &p->d_list_src}, {&hs.pair, &p->d_list_pair}, {&hs.item, &p->d_list_item}}, st);
 }
 
 // The boxes whose tables, coefficients and stored own profile values a call on the listed
@@ -954,8 +955,8 @@ int upload_scope(celeste_plan* p, const HostScope& hs, bool stored, Scope* rende
     if (stored) neighbour_lists(p, hs, npair, nitem);
     const bool restrict_render = stored && 2 * nitem.size() < p->cut->items.size();
     if (restrict_render)
-        CHK(upload(p, {{&hs.src, p->d_list_src}, {&hs.pair, p->d_list_pair}, {&hs.item, p->d_list_item},
-                       {&npair, p->d_list_npair}, {&nitem, p->d_list_nitem}},
+        CHK(upload(p, {{&hs.src, &p->d_list_src}, {&hs.pair, &p->d_list_pair}, {&hs.item, &p->d_list_item},
+                       {&npair, &p->d_list_npair}, {&nitem, &p->d_list_nitem}},
                    st));
     else
         CHK(upload_lists(p, hs, st));
@@ -1134,10 +1135,9 @@ void celeste_plan_destroy(celeste_plan* p) {
     void* bufs[] = {p->d_images, p->d_pairs, p->d_items, p->d_nbr, p->d_tiles, p->d_tile_list, p->d_patch_ptr,
                     p->d_tab1, p->d_coef1, p->d_tab2, p->d_coef2, p->d_partials, p->d_E, p->d_V, p->d_bg,
                     p->d_tile_sums, p->d_status, p->d_counter, p->d_grad, p->d_hess, p->d_theta_trial,
-                    p->d_pred, p->d_elbo_cur, p->d_elbo_trial, p->d_radius, p->d_done, p->d_list_src,
-                    p->d_list_pair, p->d_list_item, p->d_cls_items, p->d_pair_lgamma, p->d_fg, p->d_gw,
+                    p->d_pred, p->d_elbo_cur, p->d_elbo_trial, p->d_radius, p->d_done, p->d_list, p->d_cls_items, p->d_pair_lgamma, p->d_fg, p->d_gw,
                     p->d_hw, p->d_kk, p->d_hg, p->d_nu, p->d_accepted, p->d_live,
-                    p->d_mix, p->d_scalar, p->d_tt_part, p->d_list_npair, p->d_list_nitem, p->d_wcount};
+                    p->d_mix, p->d_scalar, p->d_tt_part, p->d_wcount};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
@@ -1256,18 +1256,12 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     A(dalloc(&p->d_elbo_trial, S, W));
     A(dalloc(&p->d_radius, S, W));
     A(dalloc(&p->d_done, S, W));
-    A(dalloc(&p->d_list_src, S, W));
-    A(dalloc(&p->d_list_pair, np, W));
-    A(dalloc(&p->d_list_item, max_items, W));
-    A(dalloc(&p->d_list_npair, np, W));
-    A(dalloc(&p->d_list_nitem, max_items, W));
+    p->cap_list = S + 2 * np + 2 * max_items;
+    A(dalloc(&p->d_list, p->cap_list, W));
     A(dalloc(&p->d_cls_items, max_items, W));
     A(dalloc(&p->d_scalar, 1, W));
     A(dalloc(&p->d_tt_part, 1024, W));
     if (d->flags & CELESTE_COLOR_MIXTURE) A(dalloc(&p->d_mix, 2 * NMIX * MIXF, W));
-    p->cap_list_item = max_items;
-    p->cap_list_src = S;
-    p->cap_list_pair = np;
     if (r != CELESTE_OK) {
         celeste_plan_destroy(p);
         return r;
@@ -1511,10 +1505,7 @@ int celeste_hessian(celeste_plan* p, const double* theta, const int32_t* src, in
         CHK(background(p, si, st));
     }
     CHK(adjoint(p, si, nullptr, false, BASE_BG, true, st, 0, true));
-    CHK(hessian_from_intermediates(p, theta, ss, sp, si, BASE_BG, p->d_hess, nullptr, st));
-    const size_t np2 = (size_t)p->consts.npar * p->consts.npar;
-    HIPCHK(hipMemcpyAsync(hess, p->d_hess, (size_t)n * np2 * sizeof(double), hipMemcpyDeviceToDevice, st));
-    return CELESTE_OK;
+    return hessian_from_intermediates(p, theta, ss, sp, si, BASE_BG, hess, nullptr, st);
 }
 
 int celeste_work_counts(celeste_plan* p, const double* theta, int64_t* counts, hipStream_t st) {
@@ -1764,33 +1755,22 @@ int celeste_sweep(celeste_plan* p, double* theta, const int32_t* batch_ptr, cons
     off_src[n_batches] = (int32_t)hs.src.size();
     off_pair[n_batches] = (int32_t)hs.pair.size();
     off_item[n_batches] = (int32_t)hs.item.size();
-    // list buffers sized for one appearance of each source; grown (plan-owned) if a schedule
-    // repeats sources, after the stream has finished with the old ones
-    if (hs.src.size() > p->cap_list_src || hs.pair.size() > p->cap_list_pair || hs.item.size() > p->cap_list_item) {
+    // the list buffer is sized for one appearance of each source; grown (plan-owned) if a
+    // schedule repeats sources, after the stream has finished with the old one
+    const size_t n_list = hs.src.size() + hs.pair.size() + hs.item.size();
+    if (n_list > p->cap_list) {
         HIPCHK(hipStreamSynchronize(st));
-        int32_t *ns = nullptr, *np_ = nullptr, *ni = nullptr;
-        const size_t cs = std::max(hs.src.size(), p->cap_list_src), cp = std::max(hs.pair.size(), p->cap_list_pair),
-                     ci = std::max(hs.item.size(), p->cap_list_item);
-        if (hipMalloc((void**)&ns, cs * 4) != hipSuccess || hipMalloc((void**)&np_, cp * 4) != hipSuccess ||
-            hipMalloc((void**)&ni, ci * 4) != hipSuccess) {
-            (void)hipFree(ns);
-            (void)hipFree(np_);
-            (void)hipFree(ni);
+        int32_t* nl = nullptr;
+        if (hipMalloc((void**)&nl, n_list * sizeof(int32_t)) != hipSuccess) {
             (void)hipGetLastError();
             return CELESTE_ENOMEM;
         }
-        (void)hipFree(p->d_list_src);
-        (void)hipFree(p->d_list_pair);
-        (void)hipFree(p->d_list_item);
-        p->d_list_src = ns;
-        p->d_list_pair = np_;
-        p->d_list_item = ni;
-        p->cap_list_src = cs;
-        p->cap_list_pair = cp;
-        p->cap_list_item = ci;
+        (void)hipFree(p->d_list);
+        p->d_list = nl;
+        p->cap_list = n_list;
     }
     CHK(upload_lists(p, hs, st));
-    int32_t *dl_src = p->d_list_src, *dl_pair = p->d_list_pair, *dl_item = p->d_list_item;
+    const int32_t *dl_src = p->d_list_src, *dl_pair = p->d_list_pair, *dl_item = p->d_list_item;
     // With the strip render, the total ELBO leaves every box's own profile values and
     // coefficients current; each batch then takes its background from them, and its boxes
     // are rendered again at their new parameters before the next batch.
