@@ -41,24 +41,24 @@ FLOG_FLOPS = 20
 FRCP_FLOPS = 9
 N_STAR, N_GAL = 3, 42                   # Gaussians per (source, image): 3 star, 3 x (8 + 6) galaxy
 
-# Strip algorithm (what runs): per strip of L rows and per Gaussian, the value and the
-# first row ratio at the top row, then per row 2 multiplies for the recurrence plus the
-# accumulation.  Both strip passes take the box's table staged in LDS, with the offsets from
-# each PSF group's shared centre formed once per group and strip (12 FLOPs), so a seed costs
-# 9 FLOPs + 2 exps.  Pass A (profile values) runs in the render's strip pass and its values
-# are stored; the fused adjoint runs the pixel terms and pass B (seed again; per row one FMA
-# and one (star) or two (galaxy) running-sum adds; per strip the moments from the running
-# sums and the fold into the ten intermediates: 11 FLOPs per star, 46 per galaxy component).
+# Strip algorithm (what runs on fields whose PSF sigmas are at least 0.82 px): per strip of L
+# rows and per Gaussian, the value and the row ratio at the strip's centre (14 FLOPs + 2 exps,
+# the offsets from each PSF group's shared centre formed once per group and strip, 12 FLOPs);
+# the row factors come from LDS.  Pass A (profile values) runs in the render's strip pass and
+# its values are stored: per row one product and one FMA, per galaxy component one product with
+# its weight.  The fused adjoint runs the pixel terms and pass B: the seed again, per row one
+# product and two (star) or three (galaxy) Horner steps, per strip the fold into the ten
+# intermediates (16 FLOPs per star, 54 per galaxy component).
 # The strip kernels leave out of a work item the Gaussians below exp(-50) of their peak on
 # all of its pixels, so the count is taken per evaluated (live) component from the library's
 # own work counts (celeste_work_counts); the zero components that pad an odd group to a pair
 # are overhead, not counted.
-SEED = 9 + 2 * FEXP_FLOPS
+SEED = 14 + 2 * FEXP_FLOPS
 GROUP = 12
-PASS_A_STRIP = {"star": SEED, "gal": SEED}
-PASS_A_VISIT = {"star": 3, "gal": 4}
-PASS_B_STRIP = {"star": SEED + 11, "gal": SEED + 46}
-PASS_B_VISIT = {"star": 5, "gal": 6}
+PASS_A_STRIP = {"star": SEED, "gal": SEED + 1}
+PASS_A_VISIT = {"star": 3, "gal": 3}
+PASS_B_STRIP = {"star": SEED + 16, "gal": SEED + 54}
+PASS_B_VISIT = {"star": 5, "gal": 7}
 PIXEL_PER_VISIT = 40 + FLOG_FLOPS + FRCP_FLOPS
 GATHER_PER_VISIT = 11
 
@@ -445,7 +445,7 @@ def main():
                 "traffic": None if traffic is None else round(traffic),
                 "traffic_algorithmic": ADJOINT_BYTES_PER_VISIT[info["render_mode"]] * visits,
                 "counted_fp64_tflops": None if counted is None else round(counted / (adj_ms * 1e-3) / 1e12, 3),
-                "kernel": "k_adjoint_strips<double, planes, grad, L=%d> (fused own-source forward + adjoint)" % L,
+                "kernel": "k_adjoint_stored<planes, L=%d> (fused own-source forward + adjoint)" % L,
                 "flops_per_launch": adj_flops, "flops_per_visit": round(adj_flops / visits, 1),
                 "live_gaussians_per_strip": round(live_per_strip, 3),
                 "flops_per_launch_without_culling": adj_full,

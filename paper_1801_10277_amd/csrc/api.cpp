@@ -237,7 +237,7 @@ void build_items(const celeste_plan* p, Cut& c) {
 // 16 items a SIMD for the whole plan,
 //   3 steps, 50 of 500 sources (9440 items of 16)  953 / 810 / 969
 //   3 steps, all of 500 sources                   2990 / 3001 / 3746
-//   2 steps, 1024 sources (19945 of 16)           5694 / 5847 / 7466
+//   3 steps, 1024 sources (19945 of 16)           5694 / 5847 / 7466
 // The plan decides, not the call's list, so a source's steps stay the same in every list.
 void choose_cuts(celeste_plan* p) {
     const int64_t full = 4 * (int64_t)p->n_cu;   // one wave per SIMD

@@ -9,6 +9,8 @@
 // evaluation up to a few ulps per row.  In the adjoint the per-row derivative terms are
 // polynomials of degree <= 2 in the row offset, so each Gaussian contributes through
 // three moments sum_k g_k, sum_k g_k k, sum_k g_k k^2 of its weighted values.
+// Where the PSFs are wide enough the value and the ratio at the strip's centre and row factors
+// shared by all lanes take the recurrence's place (stage_rows).
 //
 // Work item = a run of up to `chunk` strips of one box (strip s of a box of width w:
 // column s mod w, rows L (s / w) ... L (s / w) + L - 1 clipped to the box).  Lane j of a
@@ -1292,7 +1294,7 @@ __global__ void __launch_bounds__(256, 2) k_tangent_stored(AdjArgs a, const Item
 // k_hess_second takes anyway), so it holds no row weights and needs no second evaluation of
 // the Gaussians: on 1024 sources (1.6e7 visits) 618 -> 376 us a pass (bounded to three waves
 // per SIMD it spills 71 VGPRs and takes as long), k_hess_second 560 -> 600 us; with the row
-// factors and the dealt sums the pass takes 311 us, k_hess_second 584.
+// factors and the dealt sums the pass takes 311 us, k_hess_second since then 415.
 // At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
 // plus accumulation registers and run one wave per SIMD; with the bound they spill a few
 // hundred bytes per lane and run 17% faster (the value variants fit without spilling).
@@ -1593,7 +1595,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item
 //   Sxx_Sxx: wnu nu (N40 - 6a N20 + 3a^2 N00);   Sxx_Sxy: wnu nu (N31 - 3b N20 - 3a N11 + 3ab N00);
 //   Sxx_Syy = Sxy_Sxy: wnu nu (N22 - d N20 - a N02 - 4b N11 + (ad + 2b^2) N00);
 //   Sxy_Syy: wnu nu (N13 - 3d N11 - 3b N02 + 3bd N00);   Syy_Syy: wnu nu (N04 - 6d N02 + 3d^2 N00)
-// (the expansions of the per-pixel formulas of hess_pixels), and for a star (weight Gs):
+// (the expansions of the per-pixel formulas), and for a star (weight Gs):
 // XX, XY, YY: N20 - a N00, N11 - b N00, N02 - d N00.  The same moments give the gradient's
 // position, frac_dev and shape sums (acc, A_UX .. A_SYY): wt (N10, N01), sgn N00 and wnu
 // (N20 - a N00, N11 - b N00, N02 - d N00); N10, N01 for a star.  One pass over the components per strip
@@ -1881,7 +1883,8 @@ __global__ void __launch_bounds__(256, 2) k_hess_second(AdjArgs a, const Item* _
 // SIMD.  So a pair of lanes shares a run of twice as many rows: each takes every other
 // component for all R rows, the even lane downwards and the odd lane upwards, then they
 // exchange the farther halves of their rows' sums and each forms the products of its nearer
-// R / 2.  Runs of four rows on one lane took 748 us on 1024 sources (1.6e7 visits), this 670.
+// R / 2.  Runs of four rows on one lane took 748 us on 1024 sources (1.6e7 visits), this 670
+// (640 in blocks of one wave).
 // A run may start up to R - 1 rows outside its box, where a narrow component must not have
 // underflowed: eight rows with smooth PSFs (the exponent falls by less than 40 in seven rows
 // at the centre), four otherwise (by 450 at the narrowest PSF there may be, sigma = 0.1 px).
