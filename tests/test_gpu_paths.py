@@ -198,7 +198,7 @@ def test_hvp_over_stored_values(B, O, synth, eig, mode, rows, chunk, dynamic):
         assert np.all(np.abs(hv[s, :n] - href) <= REL * np.abs(href) + FLOOR * habs), s
 
 
-@pytest.mark.parametrize("n", [1, 64, 65, 1024, 1025])
+@pytest.mark.parametrize("n", [1, 64, 65, 256, 257, 1024, 1025])
 def test_validation_of_lists_of_one_block_and_more(B, synth, n):
     """A bad row of a listed source refuses the call wherever it stands in the list, one of an
     unlisted source does not, and the next call starts with a clear status."""
