@@ -51,9 +51,9 @@ bool finite(double v) { return std::isfinite(v); }
 
 }  // namespace
 
-// The boxes cut into strips of `rows` rows, and those into work items.
+// The boxes cut into strips of `rows` rows, and those into work items of `chunk` strips.
 struct Cut {
-    int rows = 16;
+    int rows = 16, chunk = 64;
     std::vector<Item> items;
     std::vector<int32_t> ptr;    // [n_pairs + 1] first item of each box
     Item* d_items = nullptr;     // in the plan's
@@ -76,7 +76,8 @@ struct celeste_plan {
     int n_cu = 256;
 
     // launch configuration
-    int chunk = 64, wpb = 4, grid = 0, dynamic = 0, tile_h = 16, tile_w = 16;
+    int chunk = 64, rows = 16, wpb = 4, grid = 0, dynamic = 0, tile_h = 16, tile_w = 16;
+    int max_rows = 16;         // no strip is walked higher than this (set_cut)
     bool launch_set = false;   // celeste_plan_set_launch was called
     // 0: strips per conflict-free class, 1: binned tiles, 2: stored values + tile gather,
     // 3: stored values, background gathered inside the fused adjoint (no planes)
@@ -201,22 +202,42 @@ namespace {
 // column of a box), in box order.
 int64_t strips_of(const PairDev& pd, int rows) { return (int64_t)pd.w * ((pd.h + rows - 1) / rows); }
 
+// The highest strip that may be walked where `narrowest` is the smallest eigenvalue of a PSF
+// covariance.  The passes that walk a strip from its top row start from the component's value
+// there, which must not underflow where a row below still counts.  With sigma^2 = narrowest,
+// a row that counts is within 10 sigma of the centre along the column (exp(-50), where
+// components are left out of an item) and the top row at most rows - 1 above it; with a log
+// weight above -12 the top row's value is a normal number out to sqrt(2 (708 - 12)) = 37.3
+// sigma.  So rows - 1 <= 27 sigma: 16 rows from sigma = 0.56 px, 8 from 0.26; at four the
+// narrowest PSF accepted (0.1 px) loses rows below exp(-26) of the peak, which are 4e-12 of the
+// largest moment a pass takes (the fourth) and below 1e-13 of the others.  (Plans that take the
+// row factors have sigma >= 0.82 px.)
+int highest_strip(double narrowest) {
+    const double sigma = std::sqrt(narrowest);
+    return 15.0 <= 27.0 * sigma ? 16 : 7.0 <= 27.0 * sigma ? 8 : 4;
+}
+
 int64_t count_items(const celeste_plan* p, int rows, int chunk) {
     int64_t n = 0;
     for (const PairDev& pd : p->pairs) n += (strips_of(pd, rows) + chunk - 1) / chunk;
     return n;
 }
 
-void build_items(const celeste_plan* p, Cut& c) {
+// Strips of `rows` rows, `chunk` to an item; where that is higher than max_rows, strips of
+// max_rows and as many times more of them to an item, so that an item still covers as much
+// (and a call takes no more items).
+void set_cut(const celeste_plan* p, Cut& c, int rows, int chunk) {
+    c.rows = std::min(rows, p->max_rows);
+    c.chunk = chunk * (rows / c.rows);
     c.items.clear();
     c.ptr.assign(1, 0);
     for (size_t i = 0; i < p->pairs.size(); ++i) {
         const int n = (int)strips_of(p->pairs[i], c.rows);
-        for (int s = 0; s < n; s += p->chunk) {
+        for (int s = 0; s < n; s += c.chunk) {
             Item it;
             it.pair = (int32_t)i;
             it.start = s;
-            it.count = std::min(p->chunk, n - s);
+            it.count = std::min(c.chunk, n - s);
             it.pad = 0;
             c.items.push_back(it);
         }
@@ -247,11 +268,12 @@ void choose_cuts(celeste_plan* p) {
     else if (count_items(p, 8, p->chunk) <= full)
         eval = 8;
     int n = 1;
+    int asked[3] = {p->rows};
     auto cut_of = [&](int rows) {
         for (int i = 0; i < n; ++i)
-            if (p->cuts[i].rows == rows) return &p->cuts[i];
-        p->cuts[n].rows = rows;
-        build_items(p, p->cuts[n]);
+            if (asked[i] == rows) return &p->cuts[i];
+        asked[n] = rows;
+        set_cut(p, p->cuts[n], rows, p->chunk);
         return &p->cuts[n++];
     };
     p->cut_eval = cut_of(eval);
@@ -845,7 +867,7 @@ int total_sequence(celeste_plan* p, const double* theta, double* out, hipStream_
 }
 
 int config_code(const celeste_plan* p) {
-    return ((((p->chunk * 8 + p->wpb) * 2 + p->dynamic) * 32 + p->cut->rows) * 2 + p->render_mode) * 1000003 +
+    return ((((p->cut->chunk * 8 + p->wpb) * 2 + p->dynamic) * 32 + p->cut->rows) * 2 + p->render_mode) * 1000003 +
            p->launch_grid() * 131 + p->tile_h * 7 + p->tile_w;
 }
 
@@ -1170,12 +1192,14 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     p->n_pix = d->n_pix;
     p->d_x = d->x;
     p->images.assign(d->images, d->images + d->n_img);
-    p->smooth = true;
+    double narrowest = INFINITY;   // smallest eigenvalue of a PSF covariance
     for (const celeste_image& im : p->images)
         for (const double(&ps)[6] : im.psf) {
             const double tr = ps[3] + ps[5], df = ps[3] - ps[5];
-            if (!(0.5 * (tr - std::sqrt(df * df + 4.0 * ps[4] * ps[4])) >= 2.0 / 3.0)) p->smooth = false;
+            narrowest = std::min(narrowest, 0.5 * (tr - std::sqrt(df * df + 4.0 * ps[4] * ps[4])));
         }
+    p->smooth = narrowest >= 2.0 / 3.0;
+    p->max_rows = highest_strip(narrowest);
     p->patch_ptr.assign(d->patch_ptr, d->patch_ptr + d->n_src + 1);
     std::memcpy(p->consts.exp_alpha, d->exp_alpha, sizeof(d->exp_alpha));
     std::memcpy(p->consts.exp_nu, d->exp_nu, sizeof(d->exp_nu));
@@ -1205,7 +1229,7 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
         }
     p->n_visits = voff;
     for (const celeste_image& im : p->images) p->max_pix = std::max<int64_t>(p->max_pix, (int64_t)im.H * im.W);
-    build_items(p, p->cuts[0]);
+    set_cut(p, p->cuts[0], p->rows, p->chunk);
     choose_cuts(p);
     build_nbr(p);
     build_pair_classes(p);
@@ -1316,7 +1340,7 @@ int celeste_plan_get_info(const celeste_plan* p, celeste_plan_info* info) {
     info->n_items = (int64_t)p->cuts[0].items.size();
     info->n_tiles = (int64_t)p->tiles.size();
     info->n_nbr = (int64_t)p->nbr.size();
-    info->chunk = p->chunk;
+    info->chunk = p->cuts[0].chunk;
     info->waves_per_block = p->wpb;
     info->grid_blocks = p->launch_grid();
     info->tile_h = p->tile_h;
@@ -1378,7 +1402,7 @@ int celeste_plan_set_launch(celeste_plan* p, int chunk, int wpb, int grid, int d
             p->cap_tile_list = p->tile_list.size();
         }
     }
-    p->cuts[0].rows = strip_rows;
+    p->rows = strip_rows;
     p->cut_eval = p->cut_newton = &p->cuts[0];
     p->launch_set = true;
     p->render_mode = render_mode;
@@ -1386,7 +1410,7 @@ int celeste_plan_set_launch(celeste_plan* p, int chunk, int wpb, int grid, int d
     p->wpb = wpb;
     p->grid = grid;
     p->dynamic = dynamic;
-    build_items(p, p->cuts[0]);
+    set_cut(p, p->cuts[0], strip_rows, chunk);
     build_class_items(p);
     return upload_geometry(p);
 }
@@ -1866,7 +1890,7 @@ int celeste_autotune(celeste_plan* p, const double* theta, int reps, double* bes
         return CELESTE_OK;
     };
     struct Cfg { int chunk, wpb, grid, dyn, th, tw, rows, rmode; };
-    Cfg best{p->chunk, p->wpb, p->launch_grid(), p->dynamic, p->tile_h, p->tile_w, p->cuts[0].rows, p->render_mode};
+    Cfg best{p->chunk, p->wpb, p->launch_grid(), p->dynamic, p->tile_h, p->tile_w, p->rows, p->render_mode};
     double best_t = 1e300;
     int rc = celeste_plan_set_launch(p, best.chunk, best.wpb, best.grid, best.dyn, best.th, best.tw, best.rows,
                                      best.rmode);

@@ -233,3 +233,48 @@ def test_backgrounds_of_crowded_boxes(B, O, synth, S, rows, chunk):
         Href, Habs = O.source_hessian(P, s, with_abs=True)
         assert np.all(np.abs(H[j] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
     np.testing.assert_allclose(float(plan.total_elbo(device(f.theta))[0]), O.total_elbo(P), rtol=1e-11)
+
+
+@pytest.mark.parametrize("rows", [None, 4, 8, 16])
+@pytest.mark.parametrize("sigma", [0.1, 0.2, 0.255, 0.26, 0.35, 0.55, 0.56])
+def test_narrow_psfs_at_every_strip_height(B, O, synth, sigma, rows):
+    """ELBO (batched and plain), gradient, Hessian-vector product, total ELBO and dense Hessian
+    (both modes) with PSFs down to the narrowest accepted (0.1 px), the centre near the last row
+    of a strip of any height, past it, and between rows: a component whose value underflows at
+    a strip's top row must not vanish from the strip.  Both sides of the widths from which
+    strips of 8 and of 16 rows are walked as such (7/27 and 15/27 px); below, a plan takes no
+    more work items than at the height asked for."""
+    f = synth.tiny(S=3, n_bands=2, size=51, side=33, seed=379)
+    f.img_psf[:, :, 3] = f.img_psf[:, :, 5] = sigma ** 2
+    f.img_psf[:, :, 4] = 0.0
+    for s, past in enumerate((0.05, 0.45, -0.3)):
+        box = f.boxes[f.patch_ptr[s]]
+        f.theta[s, 0:2] = box[2] + 15 + past, box[1] + 15 + past
+    plan, P = B.Plan(f), O.Problem(f)
+    if rows:
+        plan.set_launch(strip_rows=rows)
+        info, (h, w) = plan.info(), np.asarray(f.boxes)[:, 3:5].T
+        assert info["strip_rows"] == min(rows, 16 if sigma > 15 / 27 else 8 if sigma > 7 / 27 else 4)
+        assert info["n_items"] <= np.sum(-(-w * -(-h // rows) // 64))
+    th = device(f.theta)
+    v = np.random.default_rng(13).standard_normal(f.theta.shape)
+    say("narrow psf", sigma, "rows", rows)
+    e, g = (t.cpu().numpy() for t in plan.elbo_grad(th))
+    e2, g2 = (t.cpu().numpy() for t in plan.elbo_grad(th, mode=B.CELESTE_PLAIN))
+    hv = plan.hvp(th, device(v)).cpu().numpy()
+    H = [plan.hessian(th, [0, 1, 2]).cpu().numpy()]
+    plan.set_hessian_mode(1)
+    H.append(plan.hessian(th, [0, 1, 2]).cpu().numpy())
+    np.testing.assert_allclose(float(plan.total_elbo(th)[0]), O.total_elbo(P), rtol=1e-11)
+    for s in range(3):
+        val, gref, gabs = O.source_grad(P, s)
+        ref = val[0] + val[1]
+        href, habs = O.source_hvp(P, s, v[s])
+        Href, Habs = O.source_hessian(P, s, with_abs=True)
+        for got in (e[s], e2[s]):
+            assert abs(got - ref) <= REL * abs(ref) + FLOOR * abs(val[2]), s
+        for got in (g[s, :27], g2[s, :27]):
+            assert np.all(np.abs(got - gref) <= REL * np.abs(gref) + FLOOR * gabs), s
+        assert np.all(np.abs(hv[s, :27] - href) <= REL * np.abs(href) + FLOOR * habs), s
+        for got in H:
+            assert np.all(np.abs(got[s] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
