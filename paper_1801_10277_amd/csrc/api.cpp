@@ -1113,7 +1113,8 @@ int batched_elbo_grad_scratch(celeste_plan* p, const double* theta, const uint8_
     return rc;
 }
 
-int64_t plan_item_count(const celeste_plan* p) { return (int64_t)p->cuts[0].items.size(); }
+// of the cut that batched_elbo_grad_scratch takes, whose partials the scratch holds
+int64_t plan_item_count(const celeste_plan* p) { return (int64_t)p->cut_eval->items.size(); }
 
 int plan_device(const celeste_plan* p) { return p->device; }
 
