@@ -349,8 +349,8 @@ int celeste_sweep(celeste_plan* plan, double* theta_inout, const int32_t* batch_
  * takes strip_rows and waves_per_block.  Where a PSF component's narrowest sigma is below
  * 0.56 px (15/27), strips are walked at most 8 rows high, and below 0.26 px (7/27) at most 4: a
  * Gaussian that underflows at a strip's top row would vanish from all of it.  An item then
- * holds as many more strips as each is lower, and info has the rows and strips per item as
- * walked.  Rebuilds work items and render tiles
+ * holds as many more strips as each is lower (info keeps chunk and strip_rows as set).
+ * Rebuilds work items and render tiles
  * (synchronous).  If grown tile buffers cannot be allocated it returns CELESTE_ENOMEM and
  * the plan keeps its previous configuration. */
 int celeste_plan_set_launch(celeste_plan* plan, int chunk, int waves_per_block, int grid_blocks,

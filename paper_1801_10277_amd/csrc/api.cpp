@@ -1341,13 +1341,13 @@ int celeste_plan_get_info(const celeste_plan* p, celeste_plan_info* info) {
     info->n_items = (int64_t)p->cuts[0].items.size();
     info->n_tiles = (int64_t)p->tiles.size();
     info->n_nbr = (int64_t)p->nbr.size();
-    info->chunk = p->cuts[0].chunk;
+    info->chunk = p->chunk;
     info->waves_per_block = p->wpb;
     info->grid_blocks = p->launch_grid();
     info->tile_h = p->tile_h;
     info->tile_w = p->tile_w;
     info->dynamic_queue = p->dynamic;
-    info->strip_rows = p->cuts[0].rows;
+    info->strip_rows = p->rows;
     info->render_mode = p->render_mode;
     info->n_classes = p->n_class;
     info->n_params = p->consts.npar;

@@ -254,7 +254,9 @@ def test_narrow_psfs_at_every_strip_height(B, O, synth, sigma, rows):
     if rows:
         plan.set_launch(strip_rows=rows)
         info, (h, w) = plan.info(), np.asarray(f.boxes)[:, 3:5].T
-        assert info["strip_rows"] == min(rows, 16 if sigma > 15 / 27 else 8 if sigma > 7 / 27 else 4)
+        walked = min(rows, 16 if sigma > 15 / 27 else 8 if sigma > 7 / 27 else 4)
+        assert plan.work_counts(device(f.theta))["strips"] == np.sum(w * -(-h // walked))
+        assert (info["chunk"], info["strip_rows"]) == (64, rows)
         assert info["n_items"] <= np.sum(-(-w * -(-h // rows) // 64))
     th = device(f.theta)
     v = np.random.default_rng(13).standard_normal(f.theta.shape)
