@@ -169,7 +169,7 @@ typedef struct celeste_plan celeste_plan;
  * bins boxes into render tiles and work items, and allocates the plan-owned device
  * workspace, sized for every later evaluation, Hessian, Newton and sweep call.  Besides
  * this call only celeste_plan_set_launch (grown tile buffers for smaller tiles),
- * celeste_autotune (its own timing outputs) and celeste_sweep (grown list buffers when a
+ * celeste_autotune (its own timing outputs, and once the strips that Newton keeps) and celeste_sweep (grown list buffers when a
  * schedule lists sources more often than once in total) allocate device memory;
  * celeste_elbo_grad_noalloc never does.  Synchronous.  *out receives the plan.
  * Returns CELESTE_EINVAL (nothing allocated), CELESTE_ENOMEM or CELESTE_EHIP. */
@@ -358,7 +358,10 @@ int celeste_plan_set_launch(celeste_plan* plan, int chunk, int waves_per_block, 
 
 /* Times candidate launch configurations of celeste_elbo_grad (batched) on theta with
  * HIP events (median of `reps` runs each) and keeps the fastest (a candidate replaces the
- * current choice only when at least 1% faster).  Synchronous.
+ * current choice only when at least 1% faster; the first one is the plan as it is, and an
+ * error leaves it so).  Until celeste_plan_set_launch is called the strips of the Newton,
+ * Hessian and sweep passes, and the blocks of one wave, stay those of a new plan.
+ * Synchronous.
  * best_ms (host, or NULL) receives its time. */
 int celeste_autotune(celeste_plan* plan, const double* theta, int reps, double* best_ms,
                      hipStream_t stream);

@@ -84,7 +84,8 @@ struct celeste_plan {
     int render_mode = 2;
     bool use_graph = false;
     // cuts[0] is the launch configuration's; until celeste_plan_set_launch is called the passes
-    // of a smaller plan take cuts of lower strips (choose_cuts).  cut: the one in use.
+    // of a smaller plan take cuts of lower strips (choose_cuts), and celeste_autotune leaves
+    // Newton's passes theirs.  cut: the one in use.
     Cut cuts[3];
     Cut *cut = &cuts[0], *cut_eval = &cuts[0], *cut_newton = &cuts[0];
 
@@ -92,6 +93,8 @@ struct celeste_plan {
     celeste_image* d_images = nullptr;
     PairDev* d_pairs = nullptr;      // every cut's
     Item* d_items = nullptr;
+    size_t max_items = 0;            // of 4-row strips, 64 to an item: the most of any cut
+    size_t cut_bytes = 0;            // of d_pairs and d_items
     int32_t* d_nbr = nullptr;
     TileDev* d_tiles = nullptr;
     size_t cap_tiles = 0;
@@ -191,6 +194,8 @@ struct celeste_plan {
     //   3 Newton steps, 50 of 500 sources (~1700)      810 / 828;  50 of 50 (1510)     729 / 736
     // The passes at three waves a SIMD do not care (2000-source gradient: 965 / 961).
     int pass_wpb(const Sel& list) const { return launch_set || list.n <= 8 * n_cu ? wpb : 1; }
+    // their blocks: a tuned grid's number of waves
+    int pass_grid(const Sel& list) const { return grid > 0 ? grid * (wpb / pass_wpb(list)) : launch_grid(); }
     int launch_grid() const { return grid > 0 ? grid : 64 * n_cu; }
 };
 
@@ -413,18 +418,31 @@ void build_nbr(celeste_plan* p) {
     }
 }
 
-// The cuts' boxes and items on the device, one block of each kind; cuts[0], which set_launch
-// rebuilds within max_items, comes last.
-int alloc_cuts(celeste_plan* p, size_t np, size_t max_items, size_t& W) {
-    size_t n = 0, extra = 0;
+// The cuts' boxes and items on the device, one block of each kind, in place of those there;
+// cuts[0], which set_launch rebuilds within max_items, comes last.  Without memory everything
+// stays as it was.
+int alloc_cuts(celeste_plan* p) {
+    size_t n = 0, extra = 0, bytes = 0;
+    PairDev* new_pairs = nullptr;
+    Item* new_items = nullptr;
     for (const Cut& c : p->cuts)
         if (!c.ptr.empty()) {
             ++n;
             if (&c != &p->cuts[0]) extra += c.items.size();
         }
-    int r = dalloc(&p->d_pairs, n * np, W);
-    if (r == CELESTE_OK) r = dalloc(&p->d_items, extra + max_items, W);
-    if (r != CELESTE_OK) return r;
+    int r = dalloc(&new_pairs, n * p->pairs.size(), bytes);
+    if (r == CELESTE_OK) r = dalloc(&new_items, extra + p->max_items, bytes);
+    if (r != CELESTE_OK) {
+        (void)hipFree(new_pairs);
+        (void)hipGetLastError();
+        return r;
+    }
+    (void)hipFree(p->d_pairs);
+    (void)hipFree(p->d_items);
+    p->d_pairs = new_pairs;
+    p->d_items = new_items;
+    p->workspace += bytes - p->cut_bytes;
+    p->cut_bytes = bytes;
     PairDev* dp = p->d_pairs;
     Item* di = p->d_items;
     for (int k = 2; k >= 0; --k) {
@@ -468,6 +486,81 @@ void drop_graph(celeste_plan* p) {
         p->gexec = nullptr;
     }
     p->gkey_cfg = -1;
+}
+
+struct Launch {
+    int chunk, wpb, grid, dynamic, tile_h, tile_w, rows, render_mode;
+};
+
+// A (valid) launch configuration: render tiles and cuts[0] are rebuilt, graphs dropped.
+int configure(celeste_plan* p, const Launch& l) {
+    HIPCHK(hipDeviceSynchronize());
+    drop_graph(p);
+    if (l.tile_h != p->tile_h || l.tile_w != p->tile_w) {
+        const int old_h = p->tile_h, old_w = p->tile_w;
+        p->tile_h = l.tile_h;
+        p->tile_w = l.tile_w;
+        build_tiles(p);
+        // grow the tile buffers: new ones first, so that a failed allocation leaves the plan
+        // working with its previous tiles
+        TileDev* nt = nullptr;
+        double* ns = nullptr;
+        int32_t* nl = nullptr;
+        bool ok = true;
+        if (p->tiles.size() > p->cap_tiles)
+            ok = hipMalloc((void**)&nt, p->tiles.size() * sizeof(TileDev)) == hipSuccess &&
+                 hipMalloc((void**)&ns, p->tiles.size() * sizeof(double)) == hipSuccess;
+        if (ok && p->tile_list.size() > p->cap_tile_list)
+            ok = hipMalloc((void**)&nl, p->tile_list.size() * sizeof(int32_t)) == hipSuccess;
+        if (!ok) {
+            (void)hipFree(nt);
+            (void)hipFree(ns);
+            (void)hipFree(nl);
+            (void)hipGetLastError();
+            p->tile_h = old_h;
+            p->tile_w = old_w;
+            build_tiles(p);
+            return CELESTE_ENOMEM;
+        }
+        if (nt) {
+            (void)hipFree(p->d_tiles);
+            (void)hipFree(p->d_tile_sums);
+            p->d_tiles = nt;
+            p->d_tile_sums = ns;
+            p->cap_tiles = p->tiles.size();
+        }
+        if (nl) {
+            (void)hipFree(p->d_tile_list);
+            p->d_tile_list = nl;
+            p->cap_tile_list = p->tile_list.size();
+        }
+    }
+    p->rows = l.rows;
+    p->render_mode = l.render_mode;
+    p->chunk = l.chunk;
+    p->wpb = l.wpb;
+    p->grid = l.grid;
+    p->dynamic = l.dynamic;
+    set_cut(p, p->cuts[0], l.rows, l.chunk);
+    build_class_items(p);
+    return upload_geometry(p);
+}
+
+// Newton's passes keep the strips they take, in a cut of their own, before cuts[0] is tuned for
+// the gradient.
+int own_newton_cut(celeste_plan* p) {
+    if (p->launch_set || p->cut_newton != &p->cuts[0]) return CELESTE_OK;
+    HIPCHK(hipDeviceSynchronize());
+    drop_graph(p);
+    Cut& c = p->cuts[1];   // free: a plan whose Newton passes take cuts[0] has no other
+    c = p->cuts[0];
+    const int r = alloc_cuts(p);
+    if (r != CELESTE_OK) {
+        c = Cut();
+        return r;
+    }
+    p->cut_newton = &c;
+    return upload_geometry(p);
 }
 
 // ---------------------------------------------------------------- validation
@@ -742,8 +835,9 @@ int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tange
         p->fg_valid = false;
     }
     a.status = p->d_status;
-    const int grid = grid_override > 0 ? grid_override : p->launch_grid();
-    const int wpb = tangent || base == BASE_BG ? p->pass_wpb(items) : p->wpb;
+    const bool two_waves = tangent || base == BASE_BG;
+    const int grid = grid_override > 0 ? grid_override : two_waves ? p->pass_grid(items) : p->launch_grid();
+    const int wpb = two_waves ? p->pass_wpb(items) : p->wpb;
     HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, wpb, p->cut->rows, st));
     return CELESTE_OK;
 }
@@ -1019,7 +1113,7 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.dynamic = p->dynamic;
         a.counter = p->d_counter;
         a.status = p->d_status;
-        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->launch_grid(), p->pass_wpb(item), p->cut->rows, st));
+        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->pass_grid(item), p->pass_wpb(item), p->cut->rows, st));
     }
     HIPCHK(launch_pair_block(pair, p->cut->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
                              p->d_hw, active, p->d_status, st));
@@ -1237,14 +1331,13 @@ int celeste_plan_create(const celeste_problem_desc* d, celeste_plan** out) {
     build_class_items(p);
     build_tiles(p);
     // capacity of per-item buffers: the shortest strips (4 rows) and smallest chunk (64)
-    size_t max_items = 0;
-    for (const PairDev& pd : p->pairs) max_items += (size_t)((strips_of(pd, 4) + 63) / 64);
+    const size_t max_items = p->max_items = (size_t)count_items(p, 4, 64);
     const size_t np = std::max<size_t>(p->pairs.size(), 1);
     size_t& W = p->workspace;
     int r = CELESTE_OK;
     auto A = [&](int rc) { if (rc != CELESTE_OK && r == CELESTE_OK) r = rc; };
     A(dalloc(&p->d_images, p->n_img, W));
-    A(alloc_cuts(p, np, max_items, W));
+    A(alloc_cuts(p));
     A(dalloc(&p->d_nbr, std::max<size_t>(p->nbr.size(), 1), W));
     A(dalloc(&p->d_tiles, p->tiles.size(), W));
     p->cap_tiles = p->tiles.size();
@@ -1362,60 +1455,11 @@ int celeste_plan_set_launch(celeste_plan* p, int chunk, int wpb, int grid, int d
         (tile_h * tile_w != 64 && tile_h * tile_w != 128 && tile_h * tile_w != 256) ||
         (strip_rows != 4 && strip_rows != 8 && strip_rows != 16) || render_mode < 0 || render_mode > 3)
         return CELESTE_EINVAL;
-    HIPCHK(hipDeviceSynchronize());
-    drop_graph(p);
-    if (tile_h != p->tile_h || tile_w != p->tile_w) {
-        const int old_h = p->tile_h, old_w = p->tile_w;
-        p->tile_h = tile_h;
-        p->tile_w = tile_w;
-        build_tiles(p);
-        // grow the tile buffers: new ones first, so that a failed allocation leaves the plan
-        // working with its previous tiles
-        TileDev* nt = nullptr;
-        double* ns = nullptr;
-        int32_t* nl = nullptr;
-        bool ok = true;
-        if (p->tiles.size() > p->cap_tiles)
-            ok = hipMalloc((void**)&nt, p->tiles.size() * sizeof(TileDev)) == hipSuccess &&
-                 hipMalloc((void**)&ns, p->tiles.size() * sizeof(double)) == hipSuccess;
-        if (ok && p->tile_list.size() > p->cap_tile_list)
-            ok = hipMalloc((void**)&nl, p->tile_list.size() * sizeof(int32_t)) == hipSuccess;
-        if (!ok) {
-            (void)hipFree(nt);
-            (void)hipFree(ns);
-            (void)hipFree(nl);
-            (void)hipGetLastError();
-            p->tile_h = old_h;
-            p->tile_w = old_w;
-            build_tiles(p);
-            return CELESTE_ENOMEM;
-        }
-        if (nt) {
-            (void)hipFree(p->d_tiles);
-            (void)hipFree(p->d_tile_sums);
-            p->d_tiles = nt;
-            p->d_tile_sums = ns;
-            p->cap_tiles = p->tiles.size();
-        }
-        if (nl) {
-            (void)hipFree(p->d_tile_list);
-            p->d_tile_list = nl;
-            p->cap_tile_list = p->tile_list.size();
-        }
-    }
-    p->rows = strip_rows;
+    CHK(configure(p, Launch{chunk, wpb, grid, dynamic, tile_h, tile_w, strip_rows, render_mode}));
     p->cut_eval = p->cut_newton = &p->cuts[0];
     p->launch_set = true;
-    p->render_mode = render_mode;
-    p->chunk = chunk;
-    p->wpb = wpb;
-    p->grid = grid;
-    p->dynamic = dynamic;
-    set_cut(p, p->cuts[0], strip_rows, chunk);
-    build_class_items(p);
-    return upload_geometry(p);
+    return CELESTE_OK;
 }
-
 int celeste_plan_profile(celeste_plan* p, int enable, double* ms, int64_t* calls, int reset) {
     if (!p) return CELESTE_EINVAL;
     if (enable && !p->ev[0])
@@ -1880,6 +1924,7 @@ int celeste_autotune(celeste_plan* p, const double* theta, int reps, double* bes
         std::vector<double> t;
         for (int r = 0; r < reps + 1; ++r) {
             HIPCHK(hipEventRecord(e0, st));
+            const UseCut use(p, p->cut_eval);
             CHK(batched_sequence(p, theta, nullptr, true, d_elbo, d_grad, st));
             HIPCHK(hipEventRecord(e1, st));
             HIPCHK(hipEventSynchronize(e1));
@@ -1891,16 +1936,20 @@ int celeste_autotune(celeste_plan* p, const double* theta, int reps, double* bes
         ms = t[t.size() / 2];
         return CELESTE_OK;
     };
-    struct Cfg { int chunk, wpb, grid, dyn, th, tw, rows, rmode; };
-    Cfg best{p->chunk, p->wpb, p->launch_grid(), p->dynamic, p->tile_h, p->tile_w, p->rows, p->render_mode};
+    // The start is timed as it runs, on the strips its size calls for (choose_cuts); the
+    // candidates are those of a configuration that is set.
+    Cut* const start_cut = p->cut_eval;
+    const Launch start{p->chunk, p->wpb, p->grid, p->dynamic, p->tile_h, p->tile_w, p->rows, p->render_mode};
+    Launch best = start;
+    bool tuned = false;
     double best_t = 1e300;
-    int rc = celeste_plan_set_launch(p, best.chunk, best.wpb, best.grid, best.dyn, best.th, best.tw, best.rows,
-                                     best.rmode);
+    int rc = own_newton_cut(p);
     if (rc == CELESTE_OK) rc = time_cfg(best_t);
-    auto trial = [&](Cfg c) {
+    auto trial = [&](Launch c) {
         if (rc != CELESTE_OK) return;
-        rc = celeste_plan_set_launch(p, c.chunk, c.wpb, c.grid, c.dyn, c.th, c.tw, c.rows, c.rmode);
+        rc = configure(p, c);
         if (rc != CELESTE_OK) return;
+        p->cut_eval = &p->cuts[0];
         double t = 0;
         rc = time_cfg(t);
         // a candidate must beat the current choice by 1%, about the spread of the medians of
@@ -1908,46 +1957,49 @@ int celeste_autotune(celeste_plan* p, const double* theta, int reps, double* bes
         if (rc == CELESTE_OK && t < 0.99 * best_t) {
             best_t = t;
             best = c;
+            tuned = true;
         }
     };
     // render mode and strip height interact (the register footprint of the fused adjoint
     // depends on both), so they are searched jointly first; then one coordinate pass over the
     // remaining knobs, and a second joint pass at the chosen launch shape
     auto mode_rows = [&]() {
-        const Cfg start = best;
+        const Launch from = best;
         for (int m : {0, 1, 2, 3})
             for (int r : {4, 8, 16}) {
-                Cfg c = start;
-                c.rmode = m;
+                Launch c = from;
+                c.render_mode = m;
                 c.rows = r;
-                if (c.rmode != start.rmode || c.rows != start.rows) trial(c);
+                if (c.render_mode != from.render_mode || c.rows != from.rows) trial(c);
             }
     };
     mode_rows();
-    Cfg c = best;
+    Launch c = best;
     for (int ch : {64, 128, 256, 512, 1024}) { c = best; c.chunk = ch; trial(c); }
     // waves per block and grid jointly: the cost of a work item varies with the Gaussians
     // it culls, and a block holds its slots until its slowest wave ends, so smaller blocks
     // pay off most with one item per wave (the largest grid, clipped to the item count)
     {
-        const Cfg start = best;
+        const Launch from = best;
         for (int w : {1, 2, 4})
-            for (int g : {p->n_cu, 4 * p->n_cu, 16 * p->n_cu, 64 * p->n_cu, 128 * p->n_cu, 1 << 20}) {
-                c = start;
+            for (int g : {p->n_cu, 4 * p->n_cu, 16 * p->n_cu, 0, 128 * p->n_cu, 1 << 20}) {
+                c = from;
                 c.wpb = w;
                 c.grid = g;
-                if (c.wpb != start.wpb || c.grid != start.grid) trial(c);
+                if (c.wpb != from.wpb || c.grid != from.grid) trial(c);
             }
     }
-    for (int d : {0, 1}) { c = best; c.dyn = d; trial(c); }
-    if (best.rmode == 1 || best.rmode == 2) {
+    for (int d : {0, 1}) { c = best; c.dynamic = d; trial(c); }
+    if (best.render_mode == 1 || best.render_mode == 2) {
         const int tiles[5][2] = {{8, 8}, {4, 16}, {16, 8}, {8, 16}, {16, 16}};
-        for (auto& tl : tiles) { c = best; c.th = tl[0]; c.tw = tl[1]; trial(c); }
+        for (auto& tl : tiles) { c = best; c.tile_h = tl[0]; c.tile_w = tl[1]; trial(c); }
     }
     mode_rows();
-    if (rc == CELESTE_OK)
-        rc = celeste_plan_set_launch(p, best.chunk, best.wpb, best.grid, best.dyn, best.th, best.tw, best.rows,
-                                     best.rmode);
+    // the fastest candidate if one beat the start, else (or after an error) the start again
+    if (rc != CELESTE_OK) tuned = false;
+    const int rs = configure(p, tuned ? best : start);
+    p->cut_eval = tuned ? &p->cuts[0] : start_cut;
+    if (rc == CELESTE_OK) rc = rs;
     p->use_graph = graph;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

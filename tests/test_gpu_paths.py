@@ -291,3 +291,39 @@ def test_work_counts_are_those_of_the_strips_walked(B, synth, S, side, rows):
     at.set_launch(strip_rows=rows)
     say("work counts", S, "rows", rows)
     assert new.work_counts(device(f.theta)) == at.work_counts(device(f.theta))
+
+
+@pytest.mark.parametrize("S,side", [(8, 160), (50, 300), (500, 860), (1100, 1000)])
+def test_tuning_the_gradient_leaves_the_newton_passes_their_strips(B, synth, S, side):
+    """celeste_autotune times the batched gradient: afterwards the dense Hessians, Newton steps
+    and sweeps of a plan still take the strips its size calls for (bit for bit a new plan's
+    results, as long as the tuned render mode keeps the stored values they start from), a
+    second tuning included; set_launch then sets every pass."""
+    f = synth.sdss_field(S, H=side, W=side, seed=353)
+    th = device(f.theta)
+    src = np.arange(0, S, 1 + S // 20, dtype=np.int32)
+
+    def steps(p):
+        t = th.clone()
+        e, r = p.newton(t, src, 2)
+        t2 = th.clone()
+        bp, bs = p.color_batches(3)
+        p.sweep(t2, bp, bs, 1, B.tr_params(newton_steps=1))   # (its trace adds up the tuned tiles)
+        return [x.cpu().numpy() for x in (p.hessian(th, src), t, e, r, t2)]
+
+    new, tuned, again = B.Plan(f), B.Plan(f), B.Plan(f)
+    ref = steps(new)
+    for _ in range(2):
+        say("tune", S, "sources")
+        ms = tuned.autotune(th, reps=2)
+        info = tuned.info()
+        say("tuned", ms, info)
+        for a, b in zip(steps(tuned), ref):
+            if info["render_mode"] in (2, 3):
+                np.testing.assert_array_equal(a, b)
+            else:
+                np.testing.assert_allclose(a, b, rtol=1e-9, atol=1e-9 * np.abs(b).max())
+    tuned.set_launch()
+    again.set_launch()
+    for a, b in zip(steps(tuned), steps(again)):
+        np.testing.assert_array_equal(a, b)
