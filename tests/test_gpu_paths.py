@@ -327,3 +327,15 @@ def test_tuning_the_gradient_leaves_the_newton_passes_their_strips(B, synth, S, 
     again.set_launch()
     for a, b in zip(steps(tuned), steps(again)):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("mixture", [False, True])
+@pytest.mark.parametrize("S", [1, 1023, 1025, 4097, 5200])
+def test_total_elbo_of_few_and_many_sources_a_block(B, O, synth, S, mixture):
+    """The total's KL terms where a block of the reduction gets none, one, a wave's share less
+    or more one, and several passes of its waves: within the summation error of the oracle's."""
+    f = synth.tiny(S=S, n_bands=1, size=90, side=3, seed=383)
+    if mixture:
+        f = synth.with_color_mixture(f, seed=3)
+    say("total", S, "mixture", mixture)
+    np.testing.assert_allclose(float(B.Plan(f).total_elbo(device(f.theta))[0]), O.total_elbo(O.Problem(f)), rtol=1e-11)
