@@ -234,7 +234,9 @@ __global__ void __launch_bounds__(256) k_render(RenderArgs a, const TileDev* __r
 // chain rule one box per lane; the KL one prior term per lane), against eight lanes a source
 // looping over items, boxes and prior terms before.
 // Time of the gradient form: one source 11.6 -> 7.0 us, 2000 sources 19 -> 15 us (dual
-// numbers, 1024 sources: 37 -> 15 us).
+// numbers, 1024 sources: 37 -> 15 us).  Far more sources than that are bound by issue, which idle
+// lanes cost: 20000 took 31 us with eight lanes a source, 55 so, and 48 with the registers held
+// to four waves a SIMD (131 would take three; few sources take the same time).
 constexpr int FIN_BOXES = 16;   // boxes per pass of a wave (a source has a handful)
 
 // KL(q || prior) of the source whose row p[NPK] is in LDS, by one wave (every lane takes
@@ -347,7 +349,7 @@ __device__ inline T source_value(const FinArgs& a, int s, int lane) {
 }
 
 template <class T>
-__global__ void __launch_bounds__(64) k_finalize(FinArgs a) {
+__global__ void __launch_bounds__(64, sizeof(T) == sizeof(double) ? 4 : 2) k_finalize(FinArgs a) {
     if (*a.status) return;
     const int lane = threadIdx.x;
     const int j = blockIdx.x;
