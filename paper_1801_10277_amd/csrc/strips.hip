@@ -227,10 +227,12 @@ __device__ __forceinline__ void stage_derived(const double* __restrict__ tab, do
 // N0 = n_c r^-KC and q_j+1/2 = exp(-d (j + 1/2)^2 / 2) the same for every lane: with the q in
 // LDS (q_1/2 .. q_15/2 per component, staged with the table) a row of the value pass takes two
 // operations per component (p *= r, f += q p) instead of the recurrence's three, and a row of
-// the adjoint four instead of five (strip_adjoint_q).  It needs r^15 and N0 within range:
+// the adjoint four instead of five (strip_adjoint_q).  It needs r^(L-1) and N0 within range:
 // for P_yy = d <= 1.5, (b dx + d dy_c)^2 <= d (quadratic form at the centre), so where
-// log r > 40 the exponent of N0 is below -40^2 / (2 d) - 40 KC < -800: N0 is exactly 0 and r may
-// be clamped there; r^15 then stays below e^600 and N0 below e^42.  A component whose value in
+// log r > 40 the exponent of N0 is below -40^2 / (2 d) - 40 KC: -833 at 16 rows (N0 is exactly
+// 0), -673 at 8, -593 at 4.  With r clamped to e^40 there, N0 r^(L-1) stays below e^-393 of the
+// component's scale, as do the rows' true values, so that the clamp cannot be seen; r^(L-1)
+// stays below e^600 and N0 below e^42.  A component whose value in
 // some row exceeds exp(-50) of its peak has log r < 24, so the terms are formed as exactly as
 // with the recurrence from the top row.  Every component covariance holds its PSF
 // component's, so d <= 1.5 everywhere when the PSF covariances' eigenvalues are at least
@@ -1295,9 +1297,8 @@ __global__ void __launch_bounds__(256, 2) k_tangent_stored(AdjArgs a, const Item
 // the Gaussians: on 1024 sources (1.6e7 visits) 618 -> 376 us a pass (bounded to three waves
 // per SIMD it spills 71 VGPRs and takes as long), k_hess_second 560 -> 600 us; with the row
 // factors and the dealt sums the pass takes 311 us, k_hess_second since then 415.
-// At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
-// plus accumulation registers and run one wave per SIMD; with the bound they spill a few
-// hundred bytes per lane and run 17% faster (the value variants fit without spilling).
+enum KKMode { KK_NONE = 0, KK_FULL = 1, KK_PIXEL = 2 };
+
 // Whether a pass reads each box's table from LDS: the double passes that evaluate Gaussians
 // and take the background from planes, stored backgrounds or stored values.
 template <class T, int BASE, bool DERIV, bool FGM>
@@ -1306,8 +1307,10 @@ constexpr bool lds_table() {
     return BASE == BASE_BG || (DERIV && BASE == BASE_PLANES);
 }
 
-enum KKMode { KK_NONE = 0, KK_FULL = 1, KK_PIXEL = 2 };
-
+// The passes that k_adjoint_stored and k_tangent_stored do not take.
+// At least two waves per SIMD: the dual-number variants would otherwise take 256 VGPRs
+// plus accumulation registers and run one wave per SIMD; with the bound they spill a few
+// hundred bytes per lane and run 17% faster (the value variants fit without spilling).
 template <class T, int BASE, bool DERIV, int L, bool FGM, int KK, bool ROWQ>
 __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item* __restrict__ items,
                                                         const PairDev* __restrict__ pairs,
@@ -1374,7 +1377,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_strips(AdjArgs a, const Item
                 strip_geometry(p, it.start + q, L, c, r0, nrow);
                 const double px = (double)c, py0 = (double)r0;
                 if constexpr (!FGM && (DERIV ? (BASE == BASE_PLANES || BASE == BASE_BG) : (LDS_TAB && BASE == BASE_BG))) {
-                    // Own values from pass A, then the pixel rows streamed as above.
+                    // Own values from pass A, then the pixel terms row by row, the next row's
+                    // loads in flight.
                     T fs[L], fg[L], fgd[KK != KK_NONE ? L : 1];
                     if constexpr (LDS_TAB) {
                         if constexpr (ROWQ) {
