@@ -11,6 +11,8 @@
 // three moments sum_k g_k, sum_k g_k k, sum_k g_k k^2 of its weighted values.
 // Where the PSFs are wide enough the value and the ratio at the strip's centre and row factors
 // shared by all lanes take the recurrence's place (stage_rows).
+// Where they are so narrow that the value at a strip's top row could underflow above rows that
+// count, the plan cuts lower strips (highest_strip in api.cpp).
 //
 // Work item = a run of up to `chunk` strips of one box (strip s of a box of width w:
 // column s mod w, rows L (s / w) ... L (s / w) + L - 1 clipped to the box).  Lane j of a
