@@ -360,7 +360,8 @@ int celeste_plan_set_launch(celeste_plan* plan, int chunk, int waves_per_block, 
  * HIP events (median of `reps` runs each) and keeps the fastest (a candidate replaces the
  * current choice only when at least 1% faster; the first one is the plan as it is, and an
  * error leaves it so).  Until celeste_plan_set_launch is called the strips of the Newton,
- * Hessian and sweep passes, and the blocks of one wave, stay those of a new plan.
+ * Hessian and sweep passes, and the blocks and grids of their sums and of celeste_hvp's
+ * tangents, stay those of a new plan.
  * Synchronous.
  * best_ms (host, or NULL) receives its time. */
 int celeste_autotune(celeste_plan* plan, const double* theta, int reps, double* best_ms,

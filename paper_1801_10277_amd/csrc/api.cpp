@@ -193,9 +193,9 @@ struct celeste_plan {
     //   3 Newton steps, 500 of 500 sources (16925)    3003 / 2845; 120 of 120 (3770)  1108 / 1061
     //   3 Newton steps, 50 of 500 sources (~1700)      810 / 828;  50 of 50 (1510)     729 / 736
     // The passes at three waves a SIMD do not care (2000-source gradient: 965 / 961).
-    int pass_wpb(const Sel& list) const { return launch_set || list.n <= 8 * n_cu ? wpb : 1; }
-    // their blocks: a tuned grid's number of waves
-    int pass_grid(const Sel& list) const { return grid > 0 ? grid * (wpb / pass_wpb(list)) : launch_grid(); }
+    // Tuning the gradient (celeste_autotune) does not change them.
+    int pass_wpb(const Sel& list) const { return launch_set ? wpb : list.n <= 8 * n_cu ? 4 : 1; }
+    int pass_grid() const { return launch_set ? launch_grid() : 64 * n_cu; }
     int launch_grid() const { return grid > 0 ? grid : 64 * n_cu; }
 };
 
@@ -836,7 +836,7 @@ int adjoint(celeste_plan* p, const Sel& items, const uint8_t* active, bool tange
     }
     a.status = p->d_status;
     const bool two_waves = tangent || base == BASE_BG;
-    const int grid = grid_override > 0 ? grid_override : two_waves ? p->pass_grid(items) : p->launch_grid();
+    const int grid = grid_override > 0 ? grid_override : two_waves ? p->pass_grid() : p->launch_grid();
     const int wpb = two_waves ? p->pass_wpb(items) : p->wpb;
     HIPCHK(launch_adjoint(a, tangent, base, deriv, grid, wpb, p->cut->rows, st));
     return CELESTE_OK;
@@ -1113,7 +1113,7 @@ int hessian_from_intermediates(celeste_plan* p, const double* theta, const Sel& 
         a.dynamic = p->dynamic;
         a.counter = p->d_counter;
         a.status = p->d_status;
-        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->pass_grid(item), p->pass_wpb(item), p->cut->rows, st));
+        HIPCHK(launch_hess_geom(a, p->d_nu, p->d_hg, p->pass_grid(), p->pass_wpb(item), p->cut->rows, st));
     }
     HIPCHK(launch_pair_block(pair, p->cut->d_pairs, p->d_partials, p->d_kk, closed ? p->d_hg : nullptr, false, 0, p->d_gw,
                              p->d_hw, active, p->d_status, st));

@@ -856,8 +856,9 @@ constexpr int STAGED = NCP * NDF + NCP * NQ;
 // a SIMD not covering it.  So the rows are loaded RB at a time, the next RB while these are
 // worked off, the first two lots before the box's table is staged; the tables of the
 // elementary functions are read instead of computed; the eleven sums leave by the swap
-// exchanges of wave_sums_dealt.  Row weights, two lots of rows and the sums fill the 168
-// registers that three waves a SIMD allow.  2000-source field: 557 -> 535 us (four rows a lot
+// exchanges of wave_sums_dealt.  Row weights, two lots of rows and the sums take more than the 168
+// registers that three waves a SIMD allow: 21 spill at 16 rows (0.2 GB of writes a launch on the
+// 2000-source field; none at 8 and 4).  2000-source field: 557 -> 535 us (four rows a lot
 // spill 32 registers: 549), one source 27.0 -> 25.5 us.
 template <int BASE, int L, bool ROWQ>
 __global__ void __launch_bounds__(256, 3) k_adjoint_stored(AdjArgs a, const Item* __restrict__ items,
